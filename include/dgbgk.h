@@ -265,25 +265,31 @@ int dgbgk_fold(dgbgk_solver *s);
 /* Wait for all work enqueued by s. */
 int dgbgk_synchronize(dgbgk_solver *s);
 
-/* Work decomposition of the stage kernel.  mode 0: automatic (all
- * velocities of a block of elements per work-group when the tile fits in LDS,
- * else velocity tiles); 1 and 3: force the all-velocity (fused) form with one
- * work-group per element block; 2: force velocity tiles of
- * velocities_per_tile (0 = automatic: the largest of Q, Q/2, Q/4, ... that
- * fits, rounded up to a multiple of 64 where the tile count stays); 4: the
- * fused form run by persistent wave-specialised work-groups that each walk a
- * run of blocks (p <= 3, at most 256 velocity rows per block; DGBGK_EINVAL
- * otherwise).  The tiled form (up to four tiles), and the fused form with one
- * element per work-group at orders 1 and 3 (FP64 and FP32 storage), take the
- * node moments of a stage's input from the update pass of the stage before;
- * a separate pass reduces them once after the state was set (init,
- * set_state, an implicit step, a fold), and in every stage with more than
- * four tiles.  get_tiling reports *fused = 0 (velocity tiles), 1 (fused, one
- * work-group per block) or 2 (fused, persistent), and the LDS bytes per
- * work-group.  The fused forms give bit-identical results, except one
- * element per work-group at orders 1 and 3 (moments handed over: another
- * summation order); the tiled form agrees to rounding.  This exists for
- * testing and tuning. */
+/* Work decomposition of the steps.  mode 0: automatic.  Orders 1 to 4 from 8
+ * velocities on (up to about 1000; not the bf16 contractions) then run the row
+ * kernels: a wavefront takes 64 velocity rows of one element, or whole
+ * elements of fewer velocities, through a tile of its own.  What they do not
+ * cover, and everything that evaluates a given state (dgbgk_rhs with more than
+ * 64 velocities, dgbgk_wall_density, implicit steps), runs the block kernels:
+ * all velocities of a block of elements per work-group when the tile fits in
+ * LDS, else velocity tiles; get_tiling reports that decomposition.  1 and 3:
+ * the all-velocity (fused) form of the block kernels with one work-group per
+ * element block where they run (the steps as in mode 0); 2: force velocity
+ * tiles of velocities_per_tile (0 = automatic: the largest of Q, Q/2, Q/4, ...
+ * that fits, rounded up to a multiple of 64 where the tile count stays) of the
+ * block kernels, for the steps too; 4: the fused form run by persistent
+ * wave-specialised work-groups that each walk a run of blocks (p <= 3, at most
+ * 256 velocity rows per block; DGBGK_EINVAL otherwise).  The row kernels of
+ * more than 64 velocities, the tiled form (up to four tiles), and the fused
+ * form with one element per work-group at orders 1 and 3 (FP64 and FP32
+ * storage), take the node moments of a stage's input from the update pass of
+ * the stage before; a separate pass reduces them once after the state was set
+ * (init, set_state, an implicit step, a fold), and in every stage of the block
+ * kernels with more than four tiles.  get_tiling reports *fused = 0 (velocity
+ * tiles), 1 (fused, one work-group per block) or 2 (fused, persistent), and the
+ * LDS bytes per work-group.  The fused forms give bit-identical results, except
+ * one element per work-group at orders 1 and 3 (moments handed over: another
+ * summation order); the tiled form and the row kernels agree to rounding. */
 int dgbgk_set_tiling(dgbgk_solver *s, int32_t mode, int32_t velocities_per_tile);
 int dgbgk_get_tiling(const dgbgk_solver *s, int32_t *fused, int32_t *elems_per_group,
                      int32_t *velocities_per_tile, size_t *lds_bytes);
@@ -291,15 +297,16 @@ int dgbgk_get_tiling(const dgbgk_solver *s, int32_t *fused, int32_t *elems_per_g
 /* Number of RK4 steps taken since the last init / set_state. */
 int dgbgk_steps_taken(const dgbgk_solver *s, int64_t *steps);
 
-/* Elements per work-group of the fused forms (0 = automatic).  The value must
- * divide into a tile that fits in LDS; DGBGK_EINVAL otherwise (the previous
+/* Elements per work-group of the fused forms of the block kernels (0 =
+ * automatic: the steps run the row kernels where they apply, see
+ * dgbgk_set_tiling).  The value must divide into a tile that fits in LDS; DGBGK_EINVAL otherwise (the previous
  * choice is kept).  Changing it changes the summation order of the node
  * moments, so results agree with other choices to rounding, not bit for bit. */
 int dgbgk_set_block_elements(dgbgk_solver *s, int32_t elems_per_group);
 
 /* Autotuner: times `launches` right-hand-side launches on the current state
- * (the state is not modified) for every admissible number of elements per
- * work-group of the fused form (and, in FP64, velocity tiles of Q, Q/2, ...,
+ * (the state is not modified) for the automatic form and every admissible
+ * number of elements per work-group of the fused form (and, in FP64, velocity tiles of Q, Q/2, ...,
  * unless the caller forced the fused form with dgbgk_set_tiling mode 1 or 3),
  * keeps the fastest and returns its average launch time in microseconds
  * (optional).  Requires a state (DGBGK_ESTATE otherwise); synchronises the
@@ -390,10 +397,11 @@ int dgbgk_implicit_step_noalloc(dgbgk_solver *s, int32_t scheme, int64_t nsteps,
 /* ---- batches: several problems advanced together ------------------------
  *
  * A batch advances n solvers (any mix of meshes, orders, velocity sets, Kn,
- * walls and precisions) in lock step: each RK4 stage is one persistent kernel
- * launch per class of (precision, order p, access width, contraction,
- * reference form, LDS size) that walks a device work list of (problem, element
- * block) items and reads each problem's arguments (state pointers, mesh and
+ * walls and precisions) in lock step: each RK4 stage is one kernel launch per
+ * class of (precision, order p, reference form) for members of the row kernels,
+ * or (those, access width, contraction, LDS size) for members of the block
+ * kernels, that takes a device work list of (problem, element block) items and
+ * reads each problem's arguments (state pointers, mesh and
  * velocity tables, tau, walls, and its own dt) from a device descriptor table.
  * Classes (and the large members below) are independent chains of launches:
  * the batch spreads them over up to four streams of its own, forked from and
@@ -436,7 +444,7 @@ int dgbgk_batch_step(dgbgk_batch *b, int64_t nsteps, const double *dt);
  * call returns DGBGK_ENONFINITE after filling all entries. */
 int dgbgk_batch_residuals(dgbgk_batch *b, double *r);
 
-/* Number of persistent launches per RK4 step (classes x 4 stages). */
+/* Number of launches per RK4 step (classes and large members x 4 stages). */
 int dgbgk_batch_launches_per_step(const dgbgk_batch *b, int32_t *launches);
 
 const char *dgbgk_batch_last_error(const dgbgk_batch *b);

@@ -20,6 +20,7 @@
 #include "init.hpp"
 #include "kernels32.hpp"
 #include "linalg.hpp"
+#include "rows.hpp"
 
 using namespace dgbgk;
 
@@ -52,9 +53,11 @@ bool is_ref(int precision) { return precision == DGBGK_FP32_REF || precision == 
 bool valid_precision(int precision) { return precision == DGBGK_FP64 || is_fp32(precision); }
 
 // Velocity tiles whose moment partials a state of this precision keeps.
-int part_tiles(int precision, int Np) {
+int part_tiles(int precision, int Nfp, int Q) {
   if (precision == DGBGK_FP64) return kMaxPartialTiles;
-  return (Np == 4 || Np == 16) ? 1 : 0;  // the orders that hand moments over (1 and 3)
+  const RowPlan r = is_bf(precision) ? RowPlan{} : row_plan(Nfp - 1, 1, Q, 4, is_ref(precision));
+  if (r.kind == 1) return r.nt;
+  return (Nfp == 2 || Nfp == 4) ? 1 : 0;  // the orders whose one-element blocks hand moments over (1 and 3)
 }
 
 // State registers (FP64, or the FP32 deviation), an FP64 transfer buffer for
@@ -82,10 +85,10 @@ Layout make_layout(int64_t K, int Np, int Nfp, int Q, int precision) {
   L.rref = off; off += ref ? round_up(ndof * sizeof(float)) : 0;
   L.mref = off; off += ref ? round_up((size_t)3 * K * Np * sizeof(double)) : 0;
   // moment partials of two states (the state a stage reads, the one it
-  // writes): FP64 up to kMaxPartialTiles velocity tiles each; FP32 storage one
-  // (one-element blocks of orders 1 and 3)
+  // writes): FP64 up to kMaxPartialTiles velocity tiles each; FP32 storage those
+  // of its row plan, or one (one-element blocks of orders 1 and 3)
   L.part = off;
-  off += 2 * round_up((size_t)part_tiles(precision, Np) * K * 7 * Np * sizeof(double));
+  off += 2 * round_up((size_t)part_tiles(precision, Nfp, Q) * K * 7 * Np * sizeof(double));
   L.total = off;
   return L;
 }
@@ -145,6 +148,7 @@ struct dgbgk_solver {
   // launch configuration
   int fused = 1, E = 1, log2E = 0, Qt = 0, ntiles = 1, nblk = 1;
   int persistent = 0;  // fused blocks run by the persistent pipelined kernel
+  RowPlan rows;        // steps and residuals run the row kernels (kind 0: the block kernels)
   int num_cu = 256;
   size_t lds = 0;
   int tiling_mode = 0, tiling_qt = 0;
@@ -154,7 +158,7 @@ struct dgbgk_solver {
   hipGraphExec_t gexec = nullptr;
   hipStream_t cap_stream = nullptr;  // capture stream (the solver's may be the null stream)
   double graph_dt = 0.0;             // dt and launch configuration the graph was captured with
-  int graph_cfg[5] = {0, 0, 0, 0, 0};
+  int graph_cfg[6] = {0, 0, 0, 0, 0, 0};
   bool graph_partials = false;       // the captured first stage reads f_n's partials
   // implicit-step workspace (allocated at the first implicit step)
   double *imp_ws = nullptr;
@@ -226,6 +230,16 @@ int validate(const dgbgk_problem *pb, dgbgk_solver *s) {
 // strips (126 vs 129 us FP64, 68.5 vs 69.5 us FP32).
 constexpr int64_t kMaxBlockDof = 4096;
 
+// The row kernels take the steps of a solver whose decomposition the caller
+// left open (neither elements per work-group nor velocity tiles nor the
+// persistent form); a choice made by the caller or the autotuner runs the
+// block kernels in it.
+void choose_rows(dgbgk_solver *s) {
+  s->rows = RowPlan{};
+  if (s->forced_E > 0 || s->tiling_mode == 2 || s->tiling_mode == 4 || is_bf(s->prec)) return;
+  s->rows = row_plan(s->p, s->K, s->Q, is_fp32(s->prec) ? 4 : 8, is_ref(s->prec));
+}
+
 void choose_tiling32(dgbgk_solver *s) {
   const int NP = s->Np;
   const bool bf = is_bf(s->prec), ref = is_ref(s->prec);
@@ -249,6 +263,7 @@ void choose_tiling32(dgbgk_solver *s) {
 // when its LDS fits, else velocity tiles with a separate moments pass.
 void choose_tiling(dgbgk_solver *s) {
   s->part_valid = false;  // the tile decomposition of any partials changes
+  choose_rows(s);
   if (is_fp32(s->prec)) {
     choose_tiling32(s);
     return;
@@ -341,7 +356,7 @@ int ensure_device(dgbgk_solver *s) {
   s->d_mom = (double *)(b + s->lay.mom);
   s->d_rhow = (double *)(b + s->lay.rhow);
   s->d_u64 = (unsigned long long *)(b + s->lay.u64);
-  if (const int pt = part_tiles(s->prec, s->Np)) {
+  if (const int pt = part_tiles(s->prec, s->Nfp, s->Q)) {
     s->d_part[0] = (double *)(b + s->lay.part);
     s->d_part[1] = (double *)(b + s->lay.part + round_up((size_t)pt * s->K * 7 * s->Np * sizeof(double)));
   }
@@ -446,6 +461,65 @@ StageArgs base_args(const dgbgk_solver *s) {
   return a;
 }
 
+template <typename B, typename T>
+void row_common(const dgbgk_solver *s, const B &b, RowArgs<T> &a) {
+  const int N1 = s->p + 1;
+  for (int i = 0; i < (N1 * N1 + 1) / 2; ++i) a.D1[i] = b.D1[i];
+  for (int i = 0; i < N1; ++i) a.lift[i] = b.lift_lo[i];
+  a.pin = b.pin;
+  a.pout = b.pout;
+  a.rx = b.rx;
+  a.sy = b.sy;
+  a.theta_inv = b.theta_inv;
+  a.half_theta2_inv = b.half_theta2_inv;
+  a.half_theta_inv = b.half_theta_inv;
+  a.inv_tau = b.inv_tau;
+  for (int sd = 0; sd < 4; ++sd) a.wall_den_inv[sd] = b.wall_den_inv[sd];
+  a.c_acc = b.c_acc;
+  a.c_out = b.c_out;
+  a.nx = b.nx;
+  a.ny = b.ny;
+  a.K = b.K;
+  a.Q = b.Q;
+  a.wall_mask = b.wall_mask;
+  a.periodic_x = b.periodic_x;
+  a.periodic_y = b.periodic_y;
+  a.stream_nt = b.stream_nt;
+  a.stage = b.stage;
+  row_plan_args(s->rows, a);
+}
+
+// The arguments of a row-kernel launch, from those of the block kernels.
+RowArgs<double> row_args(const dgbgk_solver *s, const StageArgs &b) {
+  RowArgs<double> a;
+  std::memset(&a, 0, sizeof a);
+  a.vel = b.vel;
+  a.feqb = b.feqb;
+  a.fs = b.fs;
+  a.fn = b.fn;
+  a.out = b.out;
+  a.f1 = s->d_a;
+  a.f2 = s->d_b;
+  row_common(s, b, a);
+  return a;
+}
+RowArgs<float> row_args(const dgbgk_solver *s, const Stage32Args &b) {
+  RowArgs<float> a;
+  std::memset(&a, 0, sizeof a);
+  a.vel = b.vel;
+  a.feqb = b.feqb;
+  a.fs = b.fs;
+  a.fn = b.fn;
+  a.out = b.out;
+  a.acc = b.acc;
+  a.rref = b.rref;
+  a.mref = b.mref;
+  a.rho_ref = b.rho_ref;
+  for (int c = 0; c < 7; ++c) a.mconst[c] = b.mconst[c];
+  row_common(s, b, a);
+  return a;
+}
+
 Stage32Args base_args32(const dgbgk_solver *s) {
   Stage32Args a;
   std::memset(&a, 0, sizeof a);
@@ -496,6 +570,13 @@ void rk_coefficients(int stage, double dt, double &ca, double &co) {
   }
 }
 
+// Whether a stage runs the row kernels: with the moments of its input at hand,
+// or formed in the wavefront (wall densities are copied out by the block
+// kernels only).
+bool takes_rows(const dgbgk_solver *s, const double *pin, const double *rhow_out) {
+  return !rhow_out && (s->rows.kind == 2 || (s->rows.kind == 1 && pin));
+}
+
 // One FP32 stage on deviation arrays.
 int run_stage32(dgbgk_solver *s, int stage, const float *fs, float *out, double dt,
                 double *rhow_out, const double *pin = nullptr, double *pout = nullptr) {
@@ -512,7 +593,12 @@ int run_stage32(dgbgk_solver *s, int stage, const float *fs, float *out, double 
   rk_coefficients(stage, dt, ca, co);
   a.c_acc = (float)ca;
   a.c_out = (float)co;
-  hipError_t e = launch_stage32(s->p, a, s->lds, is_bf(s->prec), is_ref(s->prec), s->stream);
+  hipError_t e;
+  if (takes_rows(s, pin, rhow_out)) {
+    e = launch_rows32(s->p, s->rows.kind, is_ref(s->prec), row_args(s, a), s->rows.lds, s->stream);
+  } else {
+    e = launch_stage32(s->p, a, s->lds, is_bf(s->prec), is_ref(s->prec), s->stream);
+  }
   if (e != hipSuccess) return hip_fail(s, e, "FP32 stage kernel");
   return DGBGK_OK;
 }
@@ -527,7 +613,8 @@ int run_stage(dgbgk_solver *s, int stage, const void *fs_, void *out_, double dt
   const double *fs = (const double *)fs_;
   double *out = (double *)out_;
   hipError_t e;
-  if (!s->fused && !pin) {
+  const bool rows = takes_rows(s, pin, rhow_out);
+  if (!rows && !s->fused && !pin) {
     e = launch_moments(fs, s->d_vel, (int)s->K, s->p, s->Q, s->pb.nx, s->pb.ny, s->wall_mask,
                        s->wall_den_inv, s->d_mom, s->d_mom + s->K * s->Np,
                        s->d_mom + 2 * s->K * s->Np, s->wall_mask ? s->d_rhow : nullptr, s->stream);
@@ -543,7 +630,9 @@ int run_stage(dgbgk_solver *s, int stage, const void *fs_, void *out_, double dt
   a.pin = pin;
   a.pout = pout;
   rk_coefficients(stage, dt, a.c_acc, a.c_out);
-  if (s->persistent) {
+  if (rows) {
+    e = launch_rows(s->p, s->rows.kind, row_args(s, a), s->rows.lds, s->stream);
+  } else if (s->persistent) {
     const int groups = (int)std::min<int64_t>(s->nblk, (int64_t)s->num_cu);
     e = launch_stream(s->p, a, s->lds, groups, s->stream);
   } else {
@@ -1020,6 +1109,7 @@ namespace {
 // Whether the stages hand moment partials to the next (see stage_partials).
 bool uses_partials(const dgbgk_solver *s) {
   if (!s->d_part[0]) return false;
+  if (s->rows.kind) return s->rows.kind == 1;
   if (is_fp32(s->prec))  // (16-byte rows: Q Np is a multiple of 4 at these orders)
     return s->fused && s->E == 1 && handoff_moments(s->p) && ((int64_t)s->Q * s->Np) % 4 == 0;
   if (!s->fused) return s->ntiles <= kMaxPartialTiles;
@@ -1044,8 +1134,19 @@ void stage_partials(const dgbgk_solver *s, int stage, const double *&pin, double
 // others) where they are stale: after f_n was set from outside a step.
 int ensure_partials(dgbgk_solver *s) {
   if (!uses_partials(s) || s->part_valid) return DGBGK_OK;
-  hipError_t e =
-      is_fp32(s->prec)
+  hipError_t e;
+  if (s->rows.kind == 1 && is_fp32(s->prec)) {
+    Stage32Args a = base_args32(s);
+    a.fs = s->g_fn;
+    a.pout = s->d_part[0];
+    e = launch_rows_sums32(s->p, row_args(s, a), s->rows.lds, s->stream);
+  } else if (s->rows.kind == 1) {
+    StageArgs a = base_args(s);
+    a.fs = s->d_fn;
+    a.pout = s->d_part[0];
+    e = launch_rows_sums(s->p, row_args(s, a), s->rows.lds, s->stream);
+  } else
+    e = is_fp32(s->prec)
           ? launch_moment_rows32(s->g_fn, s->d_vel, (int)s->K, s->Np, s->Q, s->d_part[0], s->stream)
           : launch_moment_rows(s->d_fn, s->d_vel, (int)s->K, s->Np, s->Q, s->fused ? 1 : s->ntiles,
                                s->d_part[0], s->stream);
@@ -1054,29 +1155,38 @@ int ensure_partials(dgbgk_solver *s) {
   return DGBGK_OK;
 }
 
+// State buffers a stage reads and writes: 1: fn -> A, 2: A -> B, 3: B -> A,
+// 4: A -> fn, 0 (right-hand side): fn -> B.  FP64 row kernels keep every stage
+// state for the last stage instead of an accumulator: 3: B -> acc, 4: acc -> fn.
+void stage_buffers(dgbgk_solver *s, int stage, void *&fs, void *&out) {
+  void *fn = s->d_fn, *A = s->d_a, *B = s->d_b;
+  void *C = s->rows.kind && !is_fp32(s->prec) ? (void *)s->d_acc : A;
+  switch (stage) {
+    case 1: fs = fn; out = A; break;
+    case 2: fs = A; out = B; break;
+    case 3: fs = B; out = C; break;
+    case 4: fs = C; out = fn; break;
+    default: fs = fn; out = B; break;
+  }
+}
+
 // One RK4 step.  Registers: f_n, acc, and two stage buffers A/B so that a
 // stage never overwrites the state its neighbours still read.
 int enqueue_rk4_step(dgbgk_solver *s, double dt) {
-  int rc;
-  void *fn = s->d_fn, *A = s->d_a, *B = s->d_b;
-  if (uses_partials(s)) {
-    if ((rc = ensure_partials(s))) return rc;
-    void *const io[5] = {fn, A, B, A, fn};
-    for (int st = 1; st <= 4; ++st) {
-      const double *pin;
-      double *pout;
-      stage_partials(s, st, pin, pout);
-      if ((rc = run_stage(s, st, io[st - 1], io[st], dt, nullptr, pin, pout))) {
-        s->part_valid = false;
-        return rc;
-      }
+  int rc = ensure_partials(s);
+  if (rc) return rc;
+  for (int st = 1; st <= 4; ++st) {
+    const double *pin;
+    double *pout;
+    void *fs, *out;
+    stage_partials(s, st, pin, pout);
+    stage_buffers(s, st, fs, out);
+    if ((rc = run_stage(s, st, fs, out, dt, nullptr, pin, pout))) {
+      s->part_valid = false;
+      return rc;
     }
-    return DGBGK_OK;
   }
-  if ((rc = run_stage(s, 1, fn, A, dt))) return rc;
-  if ((rc = run_stage(s, 2, A, B, dt))) return rc;
-  if ((rc = run_stage(s, 3, B, A, dt))) return rc;
-  return run_stage(s, 4, A, fn, dt);
+  return DGBGK_OK;
 }
 
 void drop_solver_graph(dgbgk_solver *s) {
@@ -1121,7 +1231,7 @@ int capture_solver_graph(dgbgk_solver *s, double dt) {
     return hip_fail(s, e2, "graph capture");
   }
   s->graph_dt = dt;
-  const int cfg[5] = {s->fused, s->E, s->Qt, s->persistent, s->prec};
+  const int cfg[6] = {s->fused, s->E, s->Qt, s->persistent, s->prec, s->rows.kind};
   std::memcpy(s->graph_cfg, cfg, sizeof cfg);
   s->graph_partials = uses_partials(s);
   return DGBGK_OK;
@@ -1148,7 +1258,7 @@ int dgbgk_step(dgbgk_solver *s, int64_t nsteps, double dt) {
   if (rc) return rc;
   int64_t it = 0;
   if (s->graph_steps > 0 && nsteps >= s->graph_steps) {
-    const int cfg[5] = {s->fused, s->E, s->Qt, s->persistent, s->prec};
+    const int cfg[6] = {s->fused, s->E, s->Qt, s->persistent, s->prec, s->rows.kind};
     if (!s->gexec || s->graph_dt != dt || std::memcmp(cfg, s->graph_cfg, sizeof cfg) != 0 ||
         (s->graph_partials && !s->part_valid)) {
       // one eager step first: it sets the kernels' LDS attributes outside the capture
@@ -1419,6 +1529,7 @@ int dgbgk_autotune(dgbgk_solver *s, int32_t launches, double *best_us) {
   // a caller that forced the fused form (mode 1 or 3) keeps it
   const bool fused_only = s->tiling_mode == 1 || s->tiling_mode == 3;
   const int fmode = fused_only ? s->tiling_mode : 0;
+  cands.push_back({0, fmode, 0});  // the automatic form (row kernels where they apply)
   for (int E = 1; E <= s->K && E <= 64; E *= 2) cands.push_back({E, fmode, 0});
   if (!is_fp32(s->prec) && !fused_only)
     for (int qt = s->Q; qt >= 8; qt = (qt + 1) / 2) cands.push_back({0, 2, qt});
@@ -1437,9 +1548,16 @@ int dgbgk_autotune(dgbgk_solver *s, int32_t launches, double *best_us) {
     choose_tiling(s);
     if (!tiling_admissible(s)) continue;
     if (c.mode == 2 && s->fused) continue;
-    if ((rc = run_stage(s, 0, s->d_fn, out, 0.0))) break;  // warm-up
+    // (forms that take their input's moments from the stage before are timed
+    // with them at hand, as they run)
+    const double *pin = nullptr;
+    double *pout = nullptr;
+    if ((rc = ensure_partials(s))) break;
+    stage_partials(s, 0, pin, pout);
+    if ((rc = run_stage(s, 0, s->d_fn, out, 0.0, nullptr, pin))) break;  // warm-up
     e = hipEventRecord(e0, s->stream);
-    for (int i = 0; i < launches && e == hipSuccess && !rc; ++i) rc = run_stage(s, 0, s->d_fn, out, 0.0);
+    for (int i = 0; i < launches && e == hipSuccess && !rc; ++i)
+      rc = run_stage(s, 0, s->d_fn, out, 0.0, nullptr, pin);
     if (e == hipSuccess) e = hipEventRecord(e1, s->stream);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     float ms = 0.f;
@@ -2052,6 +2170,7 @@ struct dgbgk_batch {
   struct Class {
     int prec = DGBGK_FP64, p = 1, cw = 0, contract = 0, ref = 0, lds_bin = 0;
     int ho = 0;  // FP32: one-element members that hand their moments between stages
+    int rows = 0;  // members of the row kernels
     std::vector<int> members;  // indices into s
     std::vector<int2> items;   // (member index within the class, element block)
     size_t lds = 0;
@@ -2069,6 +2188,7 @@ struct dgbgk_batch {
   std::vector<double> dt_loaded;   // dt each member's descriptors hold (NaN: none)
   std::vector<int> E_built;        // each member's elements per block when the lists were built
   std::vector<int> fused_built;    // and its fused flag
+  std::vector<int> rows_built;     // and its row plan's kind
   // independent chains (a class, or a large member) are spread over up to
   // kBatchLanes streams forked from and joined to `stream` around each call
   // (or captured graph), so that small kernels run beside large ones
@@ -2095,19 +2215,6 @@ int bfail(dgbgk_batch *b, int code, const char *fmt, ...) {
   if (b) b->err = buf;
   else g_create_error = buf;
   return code;
-}
-
-// State buffers a stage reads and writes: 1: fn -> A, 2: A -> B, 3: B -> A,
-// 4: A -> fn, 0 (right-hand side): fn -> B.
-void stage_buffers(dgbgk_solver *s, int stage, void *&fs, void *&out) {
-  void *fn = s->d_fn, *A = s->d_a, *B = s->d_b;
-  switch (stage) {
-    case 1: fs = fn; out = A; break;
-    case 2: fs = A; out = B; break;
-    case 3: fs = B; out = A; break;
-    case 4: fs = A; out = fn; break;
-    default: fs = fn; out = B; break;
-  }
 }
 
 // Fills the host copy of the descriptors of every class, stage and member.
@@ -2138,7 +2245,12 @@ void fill_descriptors(dgbgk_batch *b, const double *dt) {
           a.c_out = (float)co;
           a.stream_nt = nt;
           stage_partials(s, stage, a.pin, a.pout);
-          std::memcpy(dst, &a, sizeof a);
+          if (c.rows) {
+            const auto ra = row_args(s, a);
+            std::memcpy(dst, &ra, sizeof ra);
+          } else {
+            std::memcpy(dst, &a, sizeof a);
+          }
         } else {
           StageArgs a = base_args(s);
           a.fs = (const double *)fs;
@@ -2150,7 +2262,12 @@ void fill_descriptors(dgbgk_batch *b, const double *dt) {
           a.c_out = co;
           a.stream_nt = nt;
           stage_partials(s, stage, a.pin, a.pout);
-          std::memcpy(dst, &a, sizeof a);
+          if (c.rows) {
+            const auto ra = row_args(s, a);
+            std::memcpy(dst, &ra, sizeof ra);
+          } else {
+            std::memcpy(dst, &a, sizeof a);
+          }
         }
       }
   }
@@ -2183,7 +2300,12 @@ int launch_class(dgbgk_batch *b, const dgbgk_batch::Class &c, int stage, hipStre
   const void *descs = b->dev + c.off_desc + (size_t)stage * nm * c.desc_size;
   const int2 *items = (const int2 *)(b->dev + c.off_items);
   hipError_t e;
-  if (is_fp32(c.prec))
+  if (c.rows && is_fp32(c.prec))
+    e = launch_batch_rows32(c.p, c.ref, stage, (const RowArgs<float> *)descs, items, (int)c.items.size(),
+                            c.lds, st);
+  else if (c.rows)
+    e = launch_batch_rows(c.p, stage, (const RowArgs<double> *)descs, items, (int)c.items.size(), c.lds, st);
+  else if (is_fp32(c.prec))
     e = launch_batch_stage32(c.p, stage, c.cw, c.contract, c.ref, c.ho, (const Stage32Args *)descs, items,
                              (int)c.items.size(), c.lds, c.groups, st);
   else
@@ -2310,24 +2432,26 @@ int dgbgk_batch_create(dgbgk_solver *const *solvers, int32_t n, void *hip_stream
     delete b;
     return rc;
   }
-  // classes of (precision, p, access width, contraction, LDS bin)
+  // classes of (precision, p, access width, contraction, LDS bin), or of
+  // (precision, p, form) for the row kernels
   const size_t bins[4] = {40 * 1024, 64 * 1024, 80 * 1024, 160 * 1024};
   for (int i = 0; i < n; ++i) {
     dgbgk_solver *s = b->s[i];
     if (std::find(b->solo.begin(), b->solo.end(), i) != b->solo.end()) continue;
     const bool f32 = is_fp32(s->prec);
-    const int cw = f32 ? (((int64_t)s->Q * s->Np) % 4 == 0 ? 4 : 1) : 0;
+    const int cw = f32 && !s->rows.kind ? (((int64_t)s->Q * s->Np) % 4 == 0 ? 4 : 1) : 0;
     const int contract = is_bf(s->prec) ? 1 : 0;
     const int ref = is_ref(s->prec) ? 1 : 0;
-    const int ho = f32 && uses_partials(s) ? 1 : 0;
+    const int rows = s->rows.kind ? 1 : 0;
+    const int ho = !rows && f32 && uses_partials(s) ? 1 : 0;
     int bin = 0;
-    while (bin < 3 && s->lds > bins[bin]) ++bin;
+    while (!rows && bin < 3 && s->lds > bins[bin]) ++bin;
     const int prec_class = f32 ? DGBGK_FP32 : DGBGK_FP64;
     size_t k = 0;
     for (; k < b->cls.size(); ++k) {
       const auto &c = b->cls[k];
       if (c.prec == prec_class && c.p == s->p && c.cw == cw && c.contract == contract && c.ref == ref &&
-          c.ho == ho && c.lds_bin == bin)
+          c.ho == ho && c.rows == rows && c.lds_bin == bin)
         break;
     }
     if (k == b->cls.size()) {
@@ -2338,21 +2462,24 @@ int dgbgk_batch_create(dgbgk_solver *const *solvers, int32_t n, void *hip_stream
       c.contract = contract;
       c.ref = ref;
       c.ho = ho;
+      c.rows = rows;
       c.lds_bin = bin;
       b->cls.push_back(c);
     }
     auto &c = b->cls[k];
     const int li = (int)c.members.size();
     c.members.push_back(i);
-    for (int blk = 0; blk < s->nblk; ++blk) c.items.push_back(make_int2(li, blk));
-    c.lds = std::max(c.lds, s->lds);
+    const int nblk = rows ? row_items(s->rows) : s->nblk;
+    for (int blk = 0; blk < nblk; ++blk) c.items.push_back(make_int2(li, blk));
+    c.lds = std::max(c.lds, rows ? row_item_lds(s->rows) : s->lds);
   }
   // device layout: per class its items, then its descriptors (5 stages x members)
   size_t off = 0;
   for (auto &c : b->cls) {
     // the kernels index the table as an array of the argument struct: the
     // stride must be exactly its size
-    c.desc_size = is_fp32(c.prec) ? sizeof(Stage32Args) : sizeof(StageArgs);
+    c.desc_size = c.rows ? (is_fp32(c.prec) ? sizeof(RowArgs<float>) : sizeof(RowArgs<double>))
+                         : (is_fp32(c.prec) ? sizeof(Stage32Args) : sizeof(StageArgs));
     c.off_items = off;
     off += round_up(c.items.size() * sizeof(int2));
     c.off_desc = off;
@@ -2423,9 +2550,11 @@ int dgbgk_batch_create(dgbgk_solver *const *solvers, int32_t n, void *hip_stream
   b->dt_loaded.assign(n, std::nan(""));
   b->E_built.resize(n);
   b->fused_built.resize(n);
+  b->rows_built.resize(n);
   for (int i = 0; i < n; ++i) {
     b->E_built[i] = b->s[i]->E;
     b->fused_built[i] = b->s[i]->fused;
+    b->rows_built[i] = b->s[i]->rows.kind;
   }
   fill_descriptors(b, nullptr);
   if ((rc = upload_descriptors(b))) {
@@ -2452,7 +2581,8 @@ int dgbgk_batch_step(dgbgk_batch *b, int64_t nsteps, const double *dt) {
   for (size_t i = 0; i < n; ++i) {
     if (!(dt[i] > 0) || !std::isfinite(dt[i])) return bfail(b, DGBGK_EINVAL, "dt[%zu] must be > 0", i);
     if (!b->s[i]->have_state) return bfail(b, DGBGK_ESTATE, "member %zu has no state", i);
-    if (b->s[i]->E != b->E_built[i] || b->s[i]->fused != b->fused_built[i])
+    if (b->s[i]->E != b->E_built[i] || b->s[i]->fused != b->fused_built[i] ||
+        b->s[i]->rows.kind != b->rows_built[i])
       return bfail(b, DGBGK_ESTATE, "member %zu was re-tiled after the batch was built", i);
   }
   bool changed = false;
@@ -2507,7 +2637,8 @@ int dgbgk_batch_residuals(dgbgk_batch *b, double *r) {
   const size_t n = b->s.size();
   for (size_t i = 0; i < n; ++i) {
     if (!b->s[i]->have_state) return bfail(b, DGBGK_ESTATE, "member %zu has no state", i);
-    if (b->s[i]->E != b->E_built[i] || b->s[i]->fused != b->fused_built[i])
+    if (b->s[i]->E != b->E_built[i] || b->s[i]->fused != b->fused_built[i] ||
+        b->s[i]->rows.kind != b->rows_built[i])
       return bfail(b, DGBGK_ESTATE, "member %zu was re-tiled after the batch was built", i);
   }
   // L(f) of every member (one stage-0 launch per class, the members' own
