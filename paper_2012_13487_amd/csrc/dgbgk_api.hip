@@ -2287,6 +2287,43 @@ int batch_partials(dgbgk_batch *b) {
   return DGBGK_OK;
 }
 
+// The order in which a class's launch takes its items (grouped by member, in
+// mesh order): work-group b runs on XCD b mod 8, and each XCD gets an eighth of
+// every member, so that neighbouring elements meet in its L2 and members of
+// different cost spread evenly.
+void xcd_order(std::vector<int2> &items) {
+  std::vector<int2> part[8];
+  size_t turn = 0;
+  for (size_t i = 0; i < items.size();) {
+    size_t e = i;
+    while (e < items.size() && items[e].x == items[i].x) ++e;
+    const size_t n = e - i;
+    for (size_t x = 0; x < 8; ++x) {
+      const size_t to = (x + turn) % 8;  // (the longer eighths in turn)
+      part[to].insert(part[to].end(), items.begin() + i + n * x / 8, items.begin() + i + n * (x + 1) / 8);
+    }
+    turn += n % 8;
+    i = e;
+  }
+  const size_t total = items.size();
+  std::vector<int2> spare;  // what an eighth holds beyond its share of the launch
+  for (size_t x = 0; x < 8; ++x) {
+    const size_t share = total / 8 + (x < total % 8 ? 1 : 0);
+    while (part[x].size() > share) {
+      spare.push_back(part[x].back());
+      part[x].pop_back();
+    }
+  }
+  for (size_t x = 0; x < 8; ++x) {
+    const size_t share = total / 8 + (x < total % 8 ? 1 : 0);
+    while (part[x].size() < share) {
+      part[x].push_back(spare.back());
+      spare.pop_back();
+    }
+  }
+  for (size_t i = 0; i < total; ++i) items[i] = part[i % 8][i / 8];
+}
+
 int upload_descriptors(dgbgk_batch *b) {
   hipError_t e = hipMemcpyAsync(b->dev, b->host.data(), b->host.size(), hipMemcpyHostToDevice,
                                 b->stream);
@@ -2473,6 +2510,8 @@ int dgbgk_batch_create(dgbgk_solver *const *solvers, int32_t n, void *hip_stream
     for (int blk = 0; blk < nblk; ++blk) c.items.push_back(make_int2(li, blk));
     c.lds = std::max(c.lds, rows ? row_item_lds(s->rows) : s->lds);
   }
+  for (auto &c : b->cls)
+    if (c.rows) xcd_order(c.items);
   // device layout: per class its items, then its descriptors (5 stages x members)
   size_t off = 0;
   for (auto &c : b->cls) {

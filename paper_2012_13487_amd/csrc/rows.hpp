@@ -91,7 +91,7 @@ struct RowArgs {
   const T *fs;         // stage input
   RowDivisor dnx;      // elements per mesh row
   int nx, ny, K, Q;
-  int kind, nw, nt, ew, nblk;  // the plan
+  int kind, nw, nt, ew, nblk, lds;  // the plan
   int strip_w, strips, strip_last, strip_row;  // strip order: work-groups per strip, whole strips, the
   RowDivisor dstrip, dw, dlast;                // last one's width, work-groups per mesh row
   RowDivisor dnt;
@@ -130,6 +130,7 @@ void row_plan_args(const RowPlan &r, RowArgs<T> &a) {
   a.nt = r.nt;
   a.ew = r.ew;
   a.nblk = r.nblk;
+  a.lds = (int)r.lds;
   a.dnx = row_divisor(a.nx);
   a.dnt = row_divisor(r.nt);
   // strips 16 elements wide, where the work-groups tile whole mesh rows
@@ -159,8 +160,13 @@ hipError_t launch_rows_sums32(int p, const RowArgs<float> &a, size_t lds, hipStr
 // Batched stages: one work-group of 256 threads per item (problem, work-group;
 // row_items of them per problem), descriptors as in launch_batch_stage, problems
 // of order p; lds: the largest row_item_lds.
-inline int row_items(const RowPlan &r) { return r.kind == 1 ? r.nblk * r.nt : (r.nblk + 3) / 4; }
-inline size_t row_item_lds(const RowPlan &r) { return r.kind == 1 ? r.lds : 4 * r.lds; }
+// A plan's work-groups of 256 threads: two elements each where two wavefronts
+// take one, else one; four wavefronts' runs of elements.
+inline int row_items(const RowPlan &r) {
+  const int per = r.kind == 2 ? 4 : r.nw == 2 ? 2 : 1;
+  return (r.nblk * r.nt + per - 1) / per;
+}
+inline size_t row_item_lds(const RowPlan &r) { return (r.kind == 2 ? 4 : r.nw == 2 ? 2 : 1) * r.lds; }
 hipError_t launch_batch_rows(int p, int stage, const RowArgs<double> *descs, const int2 *items, int nitems, size_t lds,
                              hipStream_t st);
 hipError_t launch_batch_rows32(int p, int ref, int stage, const RowArgs<float> *descs, const int2 *items, int nitems,

@@ -736,11 +736,12 @@ __device__ __forceinline__ void row_phase(const A &a, T *tile, int r, const RowI
 // of their own for the wavefronts' sums (the wall sums pass through the tiles).
 template <int P, typename T>
 __device__ __forceinline__ void rows_sums_out(const ColumnSums<T> &cs, double ws, bool wall, int wave, int lane,
-                                              int nw, const int (&nbr)[4], char *lds, double *red, double *po) {
+                                              int nw, bool on, const int (&nbr)[4], char *lds, double *red,
+                                              double *po) {
   using Sh = RowShape<P, T>;
   constexpr int N1 = Sh::N1, NP = Sh::NP, F = 4 * N1, H = 64 / F, parts = row_sum_parts(NP, sizeof(T));
   constexpr int WB = row_wave_bytes(NP, sizeof(T)) + 64 * 16;
-  if (wave < nw) {
+  if (on) {
     double *buf = reinterpret_cast<double *>(lds + wave * WB);
     reduce_columns<P, T>(cs, lane, buf, red + wave * parts * 3 * NP);
     if (wall) {
@@ -749,19 +750,21 @@ __device__ __forceinline__ void rows_sums_out(const ColumnSums<T> &cs, double ws
     }
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < 3 * NP; t += blockDim.x) {
+  if (!on) return;
+  const int tid = 64 * wave + lane;
+  for (int t = tid; t < 3 * NP; t += 64 * nw) {
     double s = 0.0;
     for (int wv = 0; wv < nw * parts; ++wv) s += red[wv * 3 * NP + t];
     po[t] = s;
   }
-  if (wall && (int)threadIdx.x < F) {
-    const int fc = threadIdx.x / N1, m = threadIdx.x - fc * N1;
+  if (wall && tid < F) {
+    const int fc = tid / N1, m = tid - fc * N1;
     if ((fc == 0 ? nbr[0] : fc == 1 ? nbr[1] : fc == 2 ? nbr[2] : nbr[3]) < 0) {
       double s = 0.0;
       for (int wv = 0; wv < nw; ++wv) {
         const double *buf = reinterpret_cast<const double *>(lds + wv * WB);
 #pragma unroll
-        for (int h = 0; h < H; ++h) s += buf[h * F + threadIdx.x];
+        for (int h = 0; h < H; ++h) s += buf[h * F + tid];
       }
       const int node = fc == 0 ? m : fc == 1 ? m * N1 + P : fc == 2 ? P * N1 + m : m * N1;
       po[(3 + fc) * NP + node] = s;
@@ -769,13 +772,15 @@ __device__ __forceinline__ void rows_sums_out(const ColumnSums<T> &cs, double ws
   }
 }
 
+// Element k, velocity tile vt, by nw wavefronts of a work-group; wave: which of
+// them; on: whether there is such an element (the barriers are passed anyway).
 template <int P, typename T, int MODE, bool REF, typename A>
-__device__ __forceinline__ void rows_element(const A &a, int k, int vt, char *lds) {
+__device__ __forceinline__ void rows_element(const A &a, int k, int vt, int wave, bool on, char *lds) {
   using Sh = RowShape<P, T>;
   using V = typename VecOf<T>::type;
   constexpr int N1 = Sh::N1, NP = Sh::NP, MS = node_values<T, REF>();
   constexpr int TB = row_wave_bytes(NP, sizeof(T)), WB = TB + 64 * 16;
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int lane = threadIdx.x & 63, tid = 64 * wave + lane;
   const int nw = a.nw, Q = a.Q;
   T *tile = reinterpret_cast<T *>(lds + wave * WB);
   d2 *ev = reinterpret_cast<d2 *>(lds + wave * WB + TB);
@@ -794,7 +799,7 @@ __device__ __forceinline__ void rows_element(const A &a, int k, int vt, char *ld
   const int nch = (vrows + 63) >> 6;
 
   const int c = vt * nw + wave;  // this wavefront's rows: 64 from 64 c
-  const bool work = wave < nw && c < nch;
+  const bool work = on && c < nch;
   const int lo = max(0, lead - 64 * c), hi = min(64, vrows - 64 * c), q0 = 64 * c - lead;
   const int q = min(max(q0 + lane, 0), Q - 1);
 
@@ -804,7 +809,8 @@ __device__ __forceinline__ void rows_element(const A &a, int k, int vt, char *ld
   RowIn<P, T> in;
   if (work) row_velocity<P, T>(a, q, in);
   double sm[3] = {0.0, 0.0, 0.0}, sw[4] = {0.0, 0.0, 0.0, 0.0}, ref[3] = {0.0, 0.0, 0.0};
-  if (tid < NP) {
+  const bool loads_moments = on && tid < NP;
+  if (loads_moments) {
     for (int t = 0; t < a.nt; ++t) {
       const double *pp = a.pin + ((size_t)t * a.K + k) * 7 * NP + tid;
 #pragma unroll
@@ -826,7 +832,7 @@ __device__ __forceinline__ void rows_element(const A &a, int k, int vt, char *ld
     tile_load<P, T>(v, a.fs + off, hi, lane);
     row_traces_load<P, T>(a, k, q, nbr[3], nbr[1], nbr[0], nbr[2], in);
   }
-  if (tid < NP) {
+  if (loads_moments) {
     node_factors_t<REF>(a, sm, ref, mom + tid * MS);
     if (wall) {
       const int i = tid % N1, j = tid / N1;
@@ -858,7 +864,7 @@ __device__ __forceinline__ void rows_element(const A &a, int k, int vt, char *ld
     }
   }
   if constexpr (MODE == 0) return;
-  rows_sums_out<P, T>(cs, ws, wall, wave, lane, nw, nbr, lds, red,
+  rows_sums_out<P, T>(cs, ws, wall, wave, lane, nw, on, nbr, lds, red,
                       a.pout + ((size_t)vt * a.K + k) * 7 * NP);
 }
 
@@ -890,7 +896,7 @@ __device__ __forceinline__ void rows_state_sums(const A &a, int k, int vt, char 
   const int r1 = (VW * w) / NP, r2 = (VW * w + VW - 1) / NP;
   const int cross = r2 > r1 ? r2 * NP - VW * w : VW;
   const int c = vt * nw + wave;
-  if (wave < nw && c < nch) {
+  if (c < nch) {
     const int lo = max(0, lead - 64 * c), hi = min(64, vrows - 64 * c), q0 = 64 * c - lead;
     V v[Sh::NLD];
     tile_load<P, T>(v, a.fs + base + (ptrdiff_t)c * 64 * NP, hi, lane);
@@ -914,7 +920,7 @@ __device__ __forceinline__ void rows_state_sums(const A &a, int k, int vt, char 
       }
     if (wall) ws += wall_sum<P, T>(a, tile, lo, hi, q0, lane, nbr);
   }
-  rows_sums_out<P, T>(cs, ws, wall, wave, lane, nw, nbr, lds, red,
+  rows_sums_out<P, T>(cs, ws, wall, wave, lane, nw, true, nbr, lds, red,
                       a.pout + ((size_t)vt * a.K + k) * 7 * NP);
 }
 
@@ -1062,48 +1068,59 @@ constexpr int row_waves() {
   return P == 1 ? 6 : P == 2 ? 5 : 4;
 }
 
-// (aimed at five, the FP32 kernels of p = 4 spill)
-template <int P, typename T>
+// (aimed at five, the FP32 kernels of p = 4 spill; aimed at three, L(f) of a
+// batch in FP64)
+template <int KIND, int P, typename T, int MODE>
 constexpr int row_waves_most() {
-  return sizeof(T) == 4 && P == 4 ? 4 : 8;
+  return P < 4 ? 8 : sizeof(T) == 4 ? 4 : KIND == kKindWave && MODE == 0 ? 2 : 8;
 }
 
 template <int KIND, int P, typename T, int MODE, bool REF, typename A>
 __device__ __forceinline__ void rows_body(const A &a, int b, int vt, char *lds) {
-  if constexpr (KIND == kKindElement) rows_element<P, T, MODE, REF>(a, b, vt, lds);
+  if constexpr (KIND == kKindElement)
+    rows_element<P, T, MODE, REF>(a, b, vt, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), true, lds);
   else if constexpr (KIND == kKindWave) rows_wave<P, T, MODE, REF>(a, b, lds);
   else rows_state_sums<P, T>(a, b, vt, lds);
 }
 
 template <int KIND, int P, typename T, int MODE, bool REF, typename A>
-__global__ __launch_bounds__(row_threads<KIND>()) __attribute__((amdgpu_waves_per_eu(row_waves<KIND, P, T, MODE>(), row_waves_most<P, T>())))
+__global__ __launch_bounds__(row_threads<KIND>()) __attribute__((amdgpu_waves_per_eu(row_waves<KIND, P, T, MODE>(), row_waves_most<KIND, P, T, MODE>())))
 void rows_kernel(const A a) {
   extern __shared__ char row_lds[];
   const int b = strip_place(xcd_run(blockIdx.x, a.nblk), a);
   rows_body<KIND, P, T, MODE, REF>(a, b, blockIdx.y, row_lds);
 }
 
-// One item of a batch: work-group `at` of the problem's plan (kind 1: element
-// and velocity tile; kind 2: four wavefronts' runs of elements).
+// One item of a batch: the at-th work-group of four wavefronts of the problem's
+// plan (kind 1: as many elements and velocity tiles as they take; kind 2: four
+// runs of elements).  Bound by how many wavefronts are in flight: a work-group
+// of two wavefronts held a slot of four.  Eight problems of 16x16 to 28x28
+// elements, p = 2 and 3, 16 to 100 velocities, per step: FP64 107 -> 83 us,
+// FP32_REF 98 -> 78 us.
 template <int P, typename T, int MODE, bool REF, typename A>
 __device__ __forceinline__ void rows_item(const A &a, int at, char *lds) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (a.kind == kKindElement) {
-    const int k = quotient(at, a.dnt);
-    rows_element<P, T, MODE, REF>(a, k, at - k * a.nt, lds);
+    const int nw = a.nw, per = nw == 2 ? 2 : 1, sub = nw == 2 ? wave >> 1 : 0;
+    const int i = at * per + sub, w = wave - sub * nw;  // (of three wavefronts' elements the fourth sits out)
+    const bool on = w < nw && i < a.nblk * a.nt;
+    const int k = on ? quotient(i, a.dnt) : 0;
+    rows_element<P, T, MODE, REF>(a, k, on ? i - k * a.nt : 0, w, on, lds + sub * a.lds);
   } else {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = 4 * at + wave;
+    const int w = 4 * at + wave;
     if (w < a.nblk)
-      rows_wave<P, T, MODE, REF>(a, w, lds + wave * row_elements_bytes(P + 1, sizeof(T), REF, a.ew));
+      rows_wave<P, T, MODE, REF>(a, w, lds + wave * a.lds);
   }
 }
 
-// One work-group per item (problem, work-group of its plan); the arguments come
-// from a descriptor table in the constant address space (scalar loads).
+// One work-group per item (problem, work-group of its plan), listed in the order
+// the XCDs take them; the arguments come from a descriptor table in the constant
+// address space (scalar loads).
 template <int P, typename T, int MODE, bool REF, typename A>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(row_waves<kKindWave, P, T, MODE>(), row_waves_most<P, T>())))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(row_waves<kKindWave, P, T, MODE>(), row_waves_most<kKindWave, P, T, MODE>())))
 void batch_rows_kernel(const A *descs, const int2 *items, int nitems) {
   extern __shared__ char row_lds[];
-  const int2 it = items[xcd_run(blockIdx.x, nitems)];
+  const int2 it = items[blockIdx.x];
   const int inst = __builtin_amdgcn_readfirstlane(it.x), at = __builtin_amdgcn_readfirstlane(it.y);
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef __attribute__((address_space(4))) const A ConstArgs;
