@@ -485,6 +485,7 @@ void row_common(const dgbgk_solver *s, const B &b, RowArgs<T> &a) {
   a.periodic_x = b.periodic_x;
   a.periodic_y = b.periodic_y;
   a.stream_nt = b.stream_nt;
+  a.resid_scale = s->resid_scale;
   a.stage = b.stage;
   row_plan_args(s->rows, a);
 }
@@ -1170,6 +1171,39 @@ void stage_buffers(dgbgk_solver *s, int stage, void *&fs, void *&out) {
   }
 }
 
+// Row kernels: the residual of f_n (max-reduced into *result) without writing
+// L(f_n); the second slot of moment sums, free between steps, takes the rate
+// sums of several velocity tiles.  Bound by the traffic of one state read: the
+// write of L and the pass that read it again are gone, and a batch's classes
+// need one launch (ten FP64 problems of up to 64x64 elements: 768 -> 245 us;
+// eight of 16x16 to 28x28: 219 -> 75 us).
+int rows_residual(dgbgk_solver *s, const double *pin, unsigned long long *result) {
+  hipError_t e;
+  if (is_fp32(s->prec)) {
+    Stage32Args b = base_args32(s);
+    b.fs = s->g_fn;
+    b.stage = kRateSums;
+    b.pin = pin;
+    b.pout = s->d_part[1];
+    RowArgs<float> a = row_args(s, b);
+    a.result = result;
+    e = launch_rows32(s->p, s->rows.kind, is_ref(s->prec), a, s->rows.lds, s->stream);
+  } else {
+    StageArgs b = base_args(s);
+    b.fs = s->d_fn;
+    b.stage = kRateSums;
+    b.pin = pin;
+    b.pout = s->d_part[1];
+    RowArgs<double> a = row_args(s, b);
+    a.result = result;
+    e = launch_rows(s->p, s->rows.kind, a, s->rows.lds, s->stream);
+  }
+  if (e == hipSuccess && s->rows.nt > 1)
+    e = launch_rate_max(s->d_part[1], (int)s->K, s->Np, s->rows.nt, s->resid_scale, result, s->stream);
+  if (e != hipSuccess) return hip_fail(s, e, "residual kernel");
+  return DGBGK_OK;
+}
+
 // One RK4 step.  Registers: f_n, acc, and two stage buffers A/B so that a
 // stage never overwrites the state its neighbours still read.
 int enqueue_rk4_step(dgbgk_solver *s, double dt) {
@@ -1350,14 +1384,13 @@ static int residual_enqueue(dgbgk_solver *s) {
   const double *pin;
   double *pout;
   stage_partials(s, 0, pin, pout);
-  if ((rc = run_stage(s, 0, s->d_fn, s->d_b, 0.0, nullptr, pin))) return rc;
   hipError_t e = launch_fill_u64(s->d_u64, 1, 0ull, s->stream);
-  if (e == hipSuccess)
-    e = is_fp32(s->prec)
-            ? launch_residual32(s->g_b, s->d_vel, (int)s->K, s->Np, s->Q, s->resid_scale, s->d_u64,
-                                s->stream)
-            : launch_residual(s->d_b, s->d_vel, (int)s->K, s->Np, s->Q, s->resid_scale, s->d_u64,
-                              s->stream);
+  if (e != hipSuccess) return hip_fail(s, e, "fill kernel");
+  if (s->rows.kind) return rows_residual(s, pin, s->d_u64);
+  if ((rc = run_stage(s, 0, s->d_fn, s->d_b, 0.0, nullptr, pin))) return rc;
+  e = is_fp32(s->prec)
+          ? launch_residual32(s->g_b, s->d_vel, (int)s->K, s->Np, s->Q, s->resid_scale, s->d_u64, s->stream)
+          : launch_residual(s->d_b, s->d_vel, (int)s->K, s->Np, s->Q, s->resid_scale, s->d_u64, s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "residual kernel");
   return DGBGK_OK;
 }
@@ -2246,7 +2279,9 @@ void fill_descriptors(dgbgk_batch *b, const double *dt) {
           a.stream_nt = nt;
           stage_partials(s, stage, a.pin, a.pout);
           if (c.rows) {
-            const auto ra = row_args(s, a);
+            if (stage == 0) a.pout = s->d_part[1];  // (the residual's rate sums)
+            auto ra = row_args(s, a);
+            ra.result = (unsigned long long *)(b->dev + b->off_res) + c.members[i];
             std::memcpy(dst, &ra, sizeof ra);
           } else {
             std::memcpy(dst, &a, sizeof a);
@@ -2263,7 +2298,9 @@ void fill_descriptors(dgbgk_batch *b, const double *dt) {
           a.stream_nt = nt;
           stage_partials(s, stage, a.pin, a.pout);
           if (c.rows) {
-            const auto ra = row_args(s, a);
+            if (stage == 0) a.pout = s->d_part[1];  // (the residual's rate sums)
+            auto ra = row_args(s, a);
+            ra.result = (unsigned long long *)(b->dev + b->off_res) + c.members[i];
             std::memcpy(dst, &ra, sizeof ra);
           } else {
             std::memcpy(dst, &a, sizeof a);
@@ -2336,12 +2373,13 @@ int launch_class(dgbgk_batch *b, const dgbgk_batch::Class &c, int stage, hipStre
   const size_t nm = c.members.size();
   const void *descs = b->dev + c.off_desc + (size_t)stage * nm * c.desc_size;
   const int2 *items = (const int2 *)(b->dev + c.off_items);
+  const int rows_stage = stage == 0 ? kRateSums : stage;  // (a batch needs L(f) for its residuals only)
   hipError_t e;
   if (c.rows && is_fp32(c.prec))
-    e = launch_batch_rows32(c.p, c.ref, stage, (const RowArgs<float> *)descs, items, (int)c.items.size(),
+    e = launch_batch_rows32(c.p, c.ref, rows_stage, (const RowArgs<float> *)descs, items, (int)c.items.size(),
                             c.lds, st);
   else if (c.rows)
-    e = launch_batch_rows(c.p, stage, (const RowArgs<double> *)descs, items, (int)c.items.size(), c.lds, st);
+    e = launch_batch_rows(c.p, rows_stage, (const RowArgs<double> *)descs, items, (int)c.items.size(), c.lds, st);
   else if (is_fp32(c.prec))
     e = launch_batch_stage32(c.p, stage, c.cw, c.contract, c.ref, c.ho, (const Stage32Args *)descs, items,
                              (int)c.items.size(), c.lds, c.groups, st);
@@ -2680,9 +2718,10 @@ int dgbgk_batch_residuals(dgbgk_batch *b, double *r) {
         b->s[i]->rows.kind != b->rows_built[i])
       return bfail(b, DGBGK_ESTATE, "member %zu was re-tiled after the batch was built", i);
   }
-  // L(f) of every member (one stage-0 launch per class, the members' own
-  // kernels for large members), then one reduction launch per member into the
-  // batch's accumulators and a single copy to the host
+  // row kernels: the largest rate of every member of a class by one launch, of
+  // large members by their own; block kernels: L(f) by one launch per class (or
+  // the member's own kernels), then a reduction per member; a single copy to
+  // the host
   unsigned long long *acc = (unsigned long long *)(b->dev + b->off_res);
   int rc = batch_partials(b);
   if (rc) return rc;
@@ -2690,10 +2729,26 @@ int dgbgk_batch_residuals(dgbgk_batch *b, double *r) {
   if (e != hipSuccess) return bfail(b, DGBGK_EDEVICE, "fill kernel: %s", hipGetErrorString(e));
   for (const auto &c : b->cls)
     if ((rc = launch_class(b, c, 0, b->stream))) return rc;
-  for (int i : b->solo)
-    if ((rc = launch_solo(b, i, 0, b->stream))) return rc;
   for (size_t i = 0; i < n; ++i) {
     dgbgk_solver *s = b->s[i];
+    const bool solo = std::find(b->solo.begin(), b->solo.end(), (int)i) != b->solo.end();
+    if (s->rows.kind) {
+      if (solo) {
+        const double *pin;
+        double *pout;
+        stage_partials(s, 0, pin, pout);
+        hipStream_t own = s->stream;
+        s->stream = b->stream;
+        rc = rows_residual(s, pin, acc + i);
+        s->stream = own;
+        if (rc) return bfail(b, rc, "member %zu: %s", i, s->err.c_str());
+      } else if (s->rows.nt > 1) {
+        e = launch_rate_max(s->d_part[1], (int)s->K, s->Np, s->rows.nt, s->resid_scale, acc + i, b->stream);
+        if (e != hipSuccess) return bfail(b, DGBGK_EDEVICE, "residual kernel: %s", hipGetErrorString(e));
+      }
+      continue;
+    }
+    if (solo && (rc = launch_solo(b, (int)i, 0, b->stream))) return rc;
     void *fs, *out;
     stage_buffers(s, 0, fs, out);
     e = is_fp32(s->prec)

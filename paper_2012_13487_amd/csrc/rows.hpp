@@ -11,6 +11,7 @@
 namespace dgbgk {
 
 constexpr int kRowMaxN1 = 5;
+constexpr int kRateSums = 5;  // the stage of launch_rows that reduces the moment rates of L(f_s) only
 constexpr int kRowMaxP = 4;  // a row's values and rates live in registers
 constexpr int kRowStripMin = 1024;  // work-groups from which their order matters to the caches
 constexpr int kRowMinQ = 8;  // fewer velocities leave most lanes of a wavefront without a row
@@ -115,7 +116,9 @@ struct RowArgs {
   double wall_den_inv[4];
   double rho_ref;      // FP32 storage: g = f - w rho_ref, and the moments of that part
   double mconst[7];
-  int stage;           // 0: out = L(f_s); 1..4: classical RK4 stage
+  double resid_scale;  // kRateSums: the largest scaled moment rate goes to *result (one velocity tile), or the
+  unsigned long long *result;  // sums to pout (several; launch_rate_max)
+  int stage;           // 0: out = L(f_s); 1..4: classical RK4 stage; kRateSums
 };
 
 // The plan for a problem of order p with Q velocities and K elements; value
@@ -151,6 +154,10 @@ void row_plan_args(const RowPlan &r, RowArgs<T> &a) {
 // One stage.
 hipError_t launch_rows(int p, int kind, const RowArgs<double> &a, size_t lds, hipStream_t st);
 hipError_t launch_rows32(int p, int kind, int ref, const RowArgs<float> &a, size_t lds, hipStream_t st);
+
+// *result = max(*result, scale |moment rate|) from the tiles' rate sums in part.
+hipError_t launch_rate_max(const double *part, int K, int Np, int nt, double scale, unsigned long long *result,
+                           hipStream_t st);
 
 // The moment sums of the state a.fs into a.pout (kind 1), by the same lanes in
 // the same order as the stages sum their outputs.

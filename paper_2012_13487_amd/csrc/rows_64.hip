@@ -54,6 +54,32 @@ hipError_t launch_rows(int p, int kind, const RowArgs<double> &a, size_t lds, hi
   }
 }
 
+namespace {
+
+// Thread: one of the 3 Np moment rates of an element.
+__global__ __launch_bounds__(256) void rate_max_kernel(const double *part, size_t KN3, int K, int np, int nt,
+                                                       double scale, unsigned long long *result) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  double m = 0.0;
+  if (i < KN3) {
+    const size_t k = i / (3 * np), o = i - k * 3 * np;
+    double s = 0.0;
+    for (int t = 0; t < nt; ++t) s += part[((size_t)t * K + k) * 7 * np + o];
+    m = fabs(s) * scale;
+  }
+  rows::max_out(m, result);
+}
+
+}  // namespace
+
+hipError_t launch_rate_max(const double *part, int K, int Np, int nt, double scale, unsigned long long *result,
+                           hipStream_t st) {
+  const size_t n = (size_t)K * 3 * Np;
+  hipLaunchKernelGGL(rate_max_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, n, K, Np, nt,
+                     scale, result);
+  return hipGetLastError();
+}
+
 hipError_t launch_rows_sums(int p, const RowArgs<double> &a, size_t lds, hipStream_t st) {
   using namespace rows;
   switch (p) {

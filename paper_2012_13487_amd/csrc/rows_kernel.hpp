@@ -304,7 +304,8 @@ __device__ __forceinline__ void row_result(const RowArgs<float> &, const float (
 // FP64, classical RK4 from the stage states (f_1 - f_n = dt/2 k_1, f_2 - f_n =
 // dt/2 k_2, f_3 - f_n = dt k_3), so that no accumulator is written: 16, 24, 24
 // and 40 bytes per value in stages 1 to 4.
-//   MODE 0: o = k        1: o = kv = f_n + dt/2 k      2: o = x + c k  (x = f_n)
+//   MODE 0: o = k (kRateSums: o is summed, not stored)
+//   MODE 1: o = kv = f_n + dt/2 k      2: o = x + c k  (x = f_n)
 //   MODE 4: o = x + [(y - x) + 2 (z - x) + (kv - x)] / 3, kv = f_3 + dt/2 k  (x = f_n, y = f_1,
 //           z = f_2; the differences are small, so the state is rounded once)
 // FP32, increment form (the state is rounded once per step): d = sum b_i dt k_i
@@ -312,7 +313,7 @@ __device__ __forceinline__ void row_result(const RowArgs<float> &, const float (
 template <typename T, int MODE>
 struct Streams {
   static constexpr bool F64 = sizeof(T) == 8;
-  static constexpr bool X = F64 ? (MODE == 2 || MODE == 4) : MODE != 0;
+  static constexpr bool X = F64 ? (MODE == 2 || MODE == 4) : MODE != 0 && MODE != kRateSums;
   static constexpr bool Y = F64 ? MODE == 4 : (MODE == 2 || MODE == 4);
   static constexpr bool Z = F64 && MODE == 4;
   static constexpr bool ACC = !F64 && (MODE == 1 || MODE == 2);
@@ -327,7 +328,7 @@ __device__ __forceinline__ double update_value(double kv, double x, double y, do
 template <int MODE>
 __device__ __forceinline__ float update_value(float kv, float x, float y, float, float ca, float co,
                                               float &an) {
-  if (MODE == 0) return kv;
+  if (MODE == 0 || MODE == kRateSums) return kv;
   if (MODE == 1) { an = ca * kv; return x + co * kv; }
   if (MODE == 2) { an = y + ca * kv; return x + co * kv; }
   return x + (y + ca * kv);
@@ -587,7 +588,8 @@ __device__ __forceinline__ void rows_update_pass(const A &a, T *tile, const d2 *
       const bool here = !clamp || rb0 <= rlast;
       const bool first = WHOLE ? here : here && rb + r1 >= lo && rb + r1 < hi;
       const bool last = WHOLE ? here : here && rb + r2 >= lo && rb + r2 < hi;
-      if (first && last) {
+      if (MODE == kRateSums) {  // (nothing is stored)
+      } else if (first && last) {
         st_stream<NT, V>(outr, pos * (unsigned)sizeof(T), o);
         if constexpr (St::ACC) st_stream<NT, V>(accr, pos * (unsigned)sizeof(T), an);
       } else if (!WHOLE && PR > 1 && (first || last)) {
@@ -732,12 +734,30 @@ __device__ __forceinline__ void row_phase(const A &a, T *tile, int r, const RowI
 
 // ---- handed-over moments: one element per work-group --------------------------
 
+// max that keeps NaN
+__device__ __forceinline__ double nan_max(double a, double b) { return (b > a || b != b) ? b : a; }
+
+// The wavefront's largest m into *result, the bit pattern of a non-negative
+// double (which orders as the values do, NaN above all).  Most wavefronts find
+// a larger value there already and leave it.
+__device__ __forceinline__ void max_out(double m, unsigned long long *result) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = nan_max(m, __shfl_xor(m, off));
+  if ((threadIdx.x & 63) == 0) {
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(fabs(m));
+    if (bits > __hip_atomic_load(result, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(result, bits);
+  }
+}
+
 // The work-group's sums from its wavefronts' columns, in a fixed order; red: LDS
 // of their own for the wavefronts' sums (the wall sums pass through the tiles).
-template <int P, typename T>
+// RATES: of one velocity tile, the sums are the node's moment rates and their
+// largest goes to *result.
+template <int P, typename T, bool RATES = false>
 __device__ __forceinline__ void rows_sums_out(const ColumnSums<T> &cs, double ws, bool wall, int wave, int lane,
                                               int nw, bool on, const int (&nbr)[4], char *lds, double *red,
-                                              double *po) {
+                                              double *po, double scale = 0.0,
+                                              unsigned long long *result = nullptr) {
   using Sh = RowShape<P, T>;
   constexpr int N1 = Sh::N1, NP = Sh::NP, F = 4 * N1, H = 64 / F, parts = row_sum_parts(NP, sizeof(T));
   constexpr int WB = row_wave_bytes(NP, sizeof(T)) + 64 * 16;
@@ -752,10 +772,16 @@ __device__ __forceinline__ void rows_sums_out(const ColumnSums<T> &cs, double ws
   __syncthreads();
   if (!on) return;
   const int tid = 64 * wave + lane;
+  double m = 0.0;
   for (int t = tid; t < 3 * NP; t += 64 * nw) {
     double s = 0.0;
     for (int wv = 0; wv < nw * parts; ++wv) s += red[wv * 3 * NP + t];
-    po[t] = s;
+    if (RATES && result) m = nan_max(m, fabs(s) * scale);
+    else po[t] = s;
+  }
+  if (RATES) {
+    if (result && 64 * wave < 3 * NP) max_out(m, result);
+    return;
   }
   if (wall && tid < F) {
     const int fc = tid / N1, m = tid - fc * N1;
@@ -856,16 +882,20 @@ __device__ __forceinline__ void rows_element(const A &a, int k, int vt, int wave
     if (wall) row_walls<P, T, REF>(a, q, rw, in);
     if (lane >= lo && lane < hi) row_phase<P, T, MODE, REF>(a, tile, lane, in, mom);
     wave_sync();
-    constexpr bool SUM = MODE != 0;
-    rows_update<P, T, MODE, REF, SUM>(a, tile, ev, off, lo, hi, lane, wall, cs);
-    if (SUM && wall) {
+    constexpr bool SUM = MODE != 0, WALLS = SUM && MODE != kRateSums;
+    rows_update<P, T, MODE, REF, SUM>(a, tile, ev, off, lo, hi, lane, WALLS && wall, cs);
+    if (WALLS && wall) {
       wave_sync();
       ws = wall_sum<P, T>(a, tile, lo, hi, q0, lane, nbr);
     }
   }
   if constexpr (MODE == 0) return;
-  rows_sums_out<P, T>(cs, ws, wall, wave, lane, nw, on, nbr, lds, red,
-                      a.pout + ((size_t)vt * a.K + k) * 7 * NP);
+  double *po = a.pout + ((size_t)vt * a.K + k) * 7 * NP;
+  if constexpr (MODE == kRateSums)
+    rows_sums_out<P, T, true>(cs, ws, false, wave, lane, nw, on, nbr, lds, red, po, a.resid_scale,
+                              a.nt == 1 ? a.result : nullptr);
+  else
+    rows_sums_out<P, T>(cs, ws, wall, wave, lane, nw, on, nbr, lds, red, po);
 }
 
 // The same sums of a state as it is (after it was set from outside a step), by
@@ -1027,6 +1057,38 @@ __device__ __forceinline__ void rows_wave(const A &a, int w, char *lds) {
   if (a.wall_mask) row_walls<P, T, REF>(a, q, rw + er * 4 * N1, in);
   if (lane >= lead && lane < hi) row_phase<P, T, MODE, REF>(a, tile, lane, in, mom + er * ES);
   wave_sync();
+  if constexpr (MODE == kRateSums) {
+    // the node's moment rates, by the lanes that summed its moments
+    double m = 0.0;
+    for (int t0 = 0; t0 < Eb * NP; t0 += per) {
+      const int h = lane / per, t = t0 + lane - h * per;
+      const int e = t / NP, n = t - e * NP;
+      double sm[3] = {0.0, 0.0, 0.0};
+      if (h < H && t < Eb * NP) {
+        const int rq = lead + e * Q;
+        for (int q = h; q < Q; q += H) {
+          T k = tile[Sh::at(rq + q, n)];
+          if constexpr (REF) k += rate_ref(a)[base + (ptrdiff_t)(rq + q) * NP + n];
+          sm[0] += (double)k;
+          sm[1] += ev[rq + q][0] * (double)k;
+          sm[2] += ev[rq + q][1] * (double)k;
+        }
+      }
+      for (int s = 1; s < H; ++s) {
+        const int from = (lane + s * per) & 63;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const double o = __shfl(sm[c], from);
+          if (h == 0) sm[c] += o;
+        }
+      }
+      if (h == 0 && t < Eb * NP)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) m = nan_max(m, fabs(sm[c]) * a.resid_scale);
+    }
+    max_out(m, a.result);
+    return;
+  }
   ColumnSums<T> cs;  // (not summed here)
   rows_update<P, T, MODE, REF, false>(a, tile, nullptr, base, lead, hi, lane, false, cs);
 }
@@ -1061,6 +1123,7 @@ constexpr int row_threads() { return KIND == kKindWave ? 64 : 256; }
 template <int KIND, int P, typename T, int MODE>
 constexpr int row_waves() {
   if (KIND == kKindSums) return 1;
+  if (MODE == kRateSums && P == 4) return sizeof(T) == 8 && KIND == kKindWave ? 2 : 3;
   if (KIND == kKindWave) return sizeof(T) == 8 ? (P <= 2 ? 4 : P == 3 ? 3 : 2) : 4;
   // (the last FP64 stage streams five arrays: with more wavefronts than three
   // its neighbours' faces fall out of L2, p = 3: 117 us with three, 130 with four)
@@ -1068,11 +1131,11 @@ constexpr int row_waves() {
   return P == 1 ? 6 : P == 2 ? 5 : 4;
 }
 
-// (aimed at five, the FP32 kernels of p = 4 spill; aimed at three, L(f) of a
-// batch in FP64)
+// (aimed at five, the FP32 kernels of p = 4 spill, their rate sums aimed at
+// four, the FP64 rate sums of a batch aimed at three)
 template <int KIND, int P, typename T, int MODE>
 constexpr int row_waves_most() {
-  return P < 4 ? 8 : sizeof(T) == 4 ? 4 : KIND == kKindWave && MODE == 0 ? 2 : 8;
+  return P < 4 ? 8 : MODE == kRateSums ? (sizeof(T) == 8 && KIND == kKindWave ? 2 : 3) : sizeof(T) == 4 ? 4 : 8;
 }
 
 template <int KIND, int P, typename T, int MODE, bool REF, typename A>
@@ -1164,6 +1227,7 @@ hipError_t launch_stage_of(int stage, const A &a, size_t lds, hipStream_t st) {
     case 2:
     case 3: return launch_one<KIND, P, T, 2, REF>(a, lds, st);
     case 4: return launch_one<KIND, P, T, 4, REF>(a, lds, st);
+    case kRateSums: return launch_one<KIND, P, T, kRateSums, REF>(a, lds, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1176,7 +1240,7 @@ hipError_t launch_kind(int kind, const A &a, size_t lds, hipStream_t st) {
 template <int P, typename T, bool REF, typename A>
 hipError_t launch_batch_p(int stage, const A *descs, const int2 *items, int nitems, size_t lds, hipStream_t st) {
   switch (stage) {
-    case 0: return launch_batch_one<P, T, 0, REF>(descs, items, nitems, lds, st);
+    case kRateSums: return launch_batch_one<P, T, kRateSums, REF>(descs, items, nitems, lds, st);
     case 1: return launch_batch_one<P, T, 1, REF>(descs, items, nitems, lds, st);
     case 2:
     case 3: return launch_batch_one<P, T, 2, REF>(descs, items, nitems, lds, st);

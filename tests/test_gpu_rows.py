@@ -106,6 +106,32 @@ def test_row_kernels_in_a_batch_match_solo(prec):
         b.close()
 
 
+@pytest.mark.parametrize("prec", PRECISIONS, ids=["fp64", "fp32", "fp32_ref"])
+@pytest.mark.parametrize("p,q", [(1, 8), (2, 9), (3, 15), (4, 31), (2, 62), (3, 65), (4, 129), (4, 321), (2, 1021)])
+def test_residual_matches_the_rates_block_kernels_write(p, q, prec):
+    """The residual reduced inside the row kernels (whole elements in a
+    wavefront, one to four velocity tiles) against the block kernels' rates
+    reduced by a pass of its own; twice the same number; a value that is NaN is reported."""
+    spec = _spec(p, q, 5, 3, "cavity")
+    print(f"[gpu] residual {spec.name} precision {prec}", flush=True)
+    g = binding.Solver.from_spec(spec, precision=prec)
+    f = workloads.perturbed_state(11 + q, g.w, g.K, g.Np, amp=0.05)
+    g.set_state(f)
+    r = [g.residual(), g.residual()]
+    before = g.get_state()
+    g.set_block_elements(1)
+    want = g.residual()
+    assert r[0] == r[1] and abs(r[0] - want) < TOL[prec] * want
+    assert np.array_equal(g.get_state(), before)
+    if prec != binding.FP32_REF:
+        g.set_block_elements(0)
+        f.reshape(-1)[f.size // 2] = np.nan
+        g.set_state(f)
+        with pytest.raises(binding.DgbgkError) as e:
+            g.residual()
+        assert e.value.code == binding.ENONFINITE
+
+
 def test_block_elements_and_tiles_choose_the_block_kernels(oracle_mod):
     """A block size or a velocity tile set by the caller keeps the block kernels
     (rounding apart from the automatic row kernels), back to automatic the row
