@@ -1728,16 +1728,45 @@ struct Implicit {
     return DGBGK_OK;
   }
 
+  // Row kernels on a state from outside a step: stage 0, out = L(in), or
+  // kJacobian, out = v + c (L(in) - Ly).  Its moment sums (kind 1) go to the slot
+  // that is free between steps, f_n's stay current.  32x32 elements, p = 3, 144
+  // velocities: a product by the block kernel and two passes 44 us, now 20 us
+  // (sums 6.7, rows 12.9; the point y + e v comes with the basis vector).
+  int rows_rate(int stage, const double *in, double *out, const double *v, const double *Ly, double c) {
+    ++rhs_evals;
+    StageArgs b = base_args(s);
+    b.fs = in;
+    b.fn = v;
+    b.out = out;
+    b.stage = stage;
+    b.c_out = c;
+    b.pout = s->d_part[1];
+    b.pin = s->d_part[1];
+    RowArgs<double> a = row_args(s, b);
+    a.f1 = Ly;
+    if (s->rows.kind == 1) {
+      const int rc = check(launch_rows_sums(s->p, a, s->rows.lds, s->stream), "moment sums");
+      if (rc) return rc;
+    }
+    return check(launch_rows(s->p, s->rows.kind, a, s->rows.lds, s->stream), "stage kernel");
+  }
+
   int rhs(const double *in, double *out) {
+    if (s->rows.kind) return rows_rate(0, in, out, nullptr, nullptr, 0.0);
     ++rhs_evals;
     return run_stage(s, 0, in, out, 0.0);
   }
 
   // out = v - h (L(y + e v) - L(y)) / e with e = eps / vnorm: the product of
-  // (I - h J(y)) with v by a forward difference.  Ly = L(y); out != v.
-  int apply(const double *v, double vnorm, const double *Ly, double *out) {
+  // (I - h J(y)) with v by a forward difference.  Ly = L(y); out != v.  formed:
+  // T holds y + e v already.
+  int apply(const double *v, double vnorm, const double *Ly, double *out, bool formed) {
     const double e = eps / vnorm;
-    int rc = check(launch_lincomb(w.n, 1.0, w.y, e, v, 0.0, nullptr, w.T, s->stream), "lincomb");
+    int rc = DGBGK_OK;
+    if (!formed)
+      rc = check(launch_lincomb(w.n, 1.0, w.y, e, v, 0.0, nullptr, w.T, s->stream), "lincomb");
+    if (!rc && s->rows.kind) return rows_rate(kJacobian, w.T, out, v, Ly, -h / e);
     if (!rc) rc = rhs(w.T, out);
     if (!rc)
       rc = check(launch_lincomb(w.n, -h / e, out, h / e, Ly, 1.0, v, out, s->stream), "lincomb");
@@ -1754,8 +1783,9 @@ struct Implicit {
     // cycle length: short cycles while they make progress, doubled (up to
     // m) after a cycle that reduces the residual by less than 10%
     int mc = std::min(kShortCycle, m);
-    rc = check(launch_lincomb(n, -1.0 / beta, w.F, 0.0, nullptr, 0.0, nullptr, Vk(0), s->stream),
-               "lincomb");
+    rc = check(launch_multi_axpy(n, 0, w.V, w.stride, w.coef, 0.0, w.F, -1.0 / beta, Vk(0), s->stream, w.y,
+                                 eps, w.T),
+               "basis vector");
     if (rc) return rc;
     bool done = false;
     while (!done) {
@@ -1765,7 +1795,7 @@ struct Implicit {
       const double beta_cycle = beta;
       for (int j = 0; j < mc; ++j) {
         double *v1 = Vk(j + 1);
-        if ((rc = apply(Vk(j), 1.0, Ly, v1))) return rc;
+        if ((rc = apply(Vk(j), 1.0, Ly, v1, true))) return rc;
         // Classical Gram-Schmidt, repeated only when the first pass cancels
         // more than half of |w| (the "twice is enough" criterion).  V_0..V_j
         // and w = V_{j+1} are consecutive, so one multi-dot over j + 2
@@ -1788,12 +1818,16 @@ struct Implicit {
         if (!std::isfinite(ww) || !std::isfinite(hh))
           return fail(s, DGBGK_ENONFINITE, "Krylov vector is not finite");
         double hn;
+        const double *hk = h1;  // what is left to subtract
         if (ww - hh > 0.5 * ww) {
           hn = std::sqrt(ww - hh);
-          e = launch_multi_axpy(n, j + 1, w.V, w.stride, h1, -1.0, v1, 1.0 / hn, v1, s->stream);
         } else {
-          e = launch_multi_axpy(n, j + 1, w.V, w.stride, h1, -1.0, v1, 1.0, v1, s->stream);
-          if (e == hipSuccess) e = launch_multi_dot(n, j + 2, w.V, w.stride, v1, w.dots, h2, s->stream);
+          if (j < kOrthBasis) {
+            e = launch_multi_orth(n, j + 1, w.V, w.stride, h1, v1, w.dots, h2, s->stream);
+          } else {
+            e = launch_multi_axpy(n, j + 1, w.V, w.stride, h1, -1.0, v1, 1.0, v1, s->stream);
+            if (e == hipSuccess) e = launch_multi_dot(n, j + 2, w.V, w.stride, v1, w.dots, h2, s->stream);
+          }
           if (e == hipSuccess)
             e = hipMemcpyAsync(host_small.data(), h2, (size_t)(j + 2) * sizeof(double),
                                hipMemcpyDeviceToHost, s->stream);
@@ -1805,10 +1839,8 @@ struct Implicit {
             hh2 += host_small[i] * host_small[i];
           }
           hn = std::sqrt(std::max(host_small[j + 1] - hh2, 0.0));
-          e = launch_multi_axpy(n, j + 1, w.V, w.stride, h2, -1.0, v1, hn > 0.0 ? 1.0 / hn : 1.0, v1,
-                                s->stream);
+          hk = h2;
         }
-        if (e != hipSuccess) return hip_fail(s, e, "Arnoldi update");
         for (int i = 0; i < j; ++i) {
           const double a = col[i], b = col[i + 1];
           col[i] = cs[i] * a + sn[i] * b;
@@ -1827,6 +1859,10 @@ struct Implicit {
           done = true;
           break;
         }
+        if (jn == mc) break;  // (the cycle's last product needs no vector of its own)
+        // V_{j+1}, and with it the point of its product
+        e = launch_multi_axpy(n, j + 1, w.V, w.stride, hk, -1.0, v1, 1.0 / hn, v1, s->stream, w.y, eps, w.T);
+        if (e != hipSuccess) return hip_fail(s, e, "Arnoldi update");
       }
       // X += V y with R y = g (upper triangular, jn columns)
       for (int i = jn - 1; i >= 0; --i) {
@@ -1848,7 +1884,7 @@ struct Implicit {
       if ((rc = dot(w.X, w.X, xn2))) return rc;
       const double xn = std::sqrt(xn2);
       if (!(xn > 0.0)) break;
-      if ((rc = apply(w.X, xn, Ly, Vk(0)))) return rc;
+      if ((rc = apply(w.X, xn, Ly, Vk(0), false))) return rc;
       if ((rc = check(launch_lincomb(n, -1.0, Vk(0), -1.0, w.F, 0.0, nullptr, Vk(0), s->stream),
                       "lincomb")))
         return rc;
@@ -1858,18 +1894,18 @@ struct Implicit {
       if (!std::isfinite(beta)) return fail(s, DGBGK_ENONFINITE, "GMRES residual is not finite");
       if (beta <= tol2) break;
       if (beta > 0.9 * beta_cycle) mc = std::min(2 * mc, m);
-      if ((rc = check(launch_lincomb(n, 1.0 / beta, Vk(0), 0.0, nullptr, 0.0, nullptr, Vk(0), s->stream),
-                      "lincomb")))
+      if ((rc = check(launch_multi_axpy(n, 0, w.V, w.stride, w.coef, 0.0, Vk(0), 1.0 / beta, Vk(0), s->stream,
+                                        w.y, eps, w.T),
+                      "basis vector")))
         return rc;
     }
     return DGBGK_OK;
   }
 
-  // apply() for a vector v of the FP32 basis; out (FP64) != T.
-  int apply32(const float *v, double vnorm, const double *Ly, double *out) {
-    const double e = eps / vnorm;
-    int rc = check(launch_lincomb_mixed(w.n, 1.0, w.y, e, v, 0.0, nullptr, w.T, s->stream), "lincomb");
-    if (!rc) rc = rhs(w.T, out);
+  // apply() for a unit vector v of the FP32 basis, T = y + eps v; out (FP64) != T.
+  int apply32(const float *v, const double *Ly, double *out) {
+    const double e = eps;
+    int rc = rhs(w.T, out);
     if (!rc)
       rc = check(launch_lincomb_mixed(w.n, -h / e, out, 1.0, v, h / e, Ly, out, s->stream), "lincomb");
     return rc;
@@ -1886,7 +1922,7 @@ struct Implicit {
     double beta = fnorm2;
     int mc = std::min(kShortCycle, m);
     rc = check(launch_multi_axpy32(n, 0, w.V32, w.stride, w.coef, 0.0, w.F, -1.0 / beta, w.W, Vk32(0),
-                                   s->stream),
+                                   s->stream, w.y, eps, w.T),
                "basis vector");
     if (rc) return rc;
     bool done = false;
@@ -1896,7 +1932,7 @@ struct Implicit {
       int jn = 0;
       const double beta_cycle = beta;
       for (int j = 0; j < mc; ++j) {
-        if ((rc = apply32(Vk32(j), 1.0, Ly, w.W))) return rc;
+        if ((rc = apply32(Vk32(j), Ly, w.W))) return rc;
         // projections on V_0..V_j and |w|^2 in one pass
         double *h1 = w.small, *h2 = w.small + (m + 1);
         hipError_t e = launch_multi_dot32(n, j + 1, w.V32, w.stride, w.W, w.dots, h1, s->stream);
@@ -1915,10 +1951,9 @@ struct Implicit {
         if (!std::isfinite(ww) || !std::isfinite(hh))
           return fail(s, DGBGK_ENONFINITE, "Krylov vector is not finite");
         double hn;
+        const double *hk = h1;
         if (ww - hh > 0.5 * ww) {
           hn = std::sqrt(ww - hh);
-          e = launch_multi_axpy32(n, j + 1, w.V32, w.stride, h1, -1.0, w.W, 1.0 / hn, w.W, Vk32(j + 1),
-                                  s->stream);
         } else {
           e = launch_multi_axpy32(n, j + 1, w.V32, w.stride, h1, -1.0, w.W, 1.0, w.W, nullptr, s->stream);
           if (e == hipSuccess) e = launch_multi_dot32(n, j + 1, w.V32, w.stride, w.W, w.dots, h2, s->stream);
@@ -1933,10 +1968,8 @@ struct Implicit {
             hh2 += host_small[i] * host_small[i];
           }
           hn = std::sqrt(std::max(host_small[j + 1] - hh2, 0.0));
-          e = launch_multi_axpy32(n, j + 1, w.V32, w.stride, h2, -1.0, w.W, hn > 0.0 ? 1.0 / hn : 1.0, w.W,
-                                  Vk32(j + 1), s->stream);
+          hk = h2;
         }
-        if (e != hipSuccess) return hip_fail(s, e, "Arnoldi update");
         for (int i = 0; i < j; ++i) {
           const double a = col[i], b = col[i + 1];
           col[i] = cs[i] * a + sn[i] * b;
@@ -1955,6 +1988,10 @@ struct Implicit {
           done = true;
           break;
         }
+        if (jn == mc) break;
+        e = launch_multi_axpy32(n, j + 1, w.V32, w.stride, hk, -1.0, w.W, 1.0 / hn, w.W, Vk32(j + 1), s->stream,
+                                w.y, eps, w.T);
+        if (e != hipSuccess) return hip_fail(s, e, "Arnoldi update");
       }
       for (int i = jn - 1; i >= 0; --i) {
         double t = g[i];
@@ -1974,7 +2011,7 @@ struct Implicit {
       if ((rc = dot(w.X, w.X, xn2))) return rc;
       const double xn = std::sqrt(xn2);
       if (!(xn > 0.0)) break;
-      if ((rc = apply(w.X, xn, Ly, w.W))) return rc;
+      if ((rc = apply(w.X, xn, Ly, w.W, false))) return rc;
       if ((rc = check(launch_lincomb(n, -1.0, w.W, -1.0, w.F, 0.0, nullptr, w.W, s->stream), "lincomb")))
         return rc;
       double r2 = 0.0;
@@ -1984,7 +2021,7 @@ struct Implicit {
       if (beta <= tol2) break;
       if (beta > 0.9 * beta_cycle) mc = std::min(2 * mc, m);
       if ((rc = check(launch_multi_axpy32(n, 0, w.V32, w.stride, w.coef, 0.0, w.W, 1.0 / beta, w.W,
-                                          Vk32(0), s->stream),
+                                          Vk32(0), s->stream, w.y, eps, w.T),
                       "basis vector")))
         return rc;
     }

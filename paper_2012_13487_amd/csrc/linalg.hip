@@ -147,11 +147,14 @@ __global__ __launch_bounds__(kBlock) void multi_dot_final_kernel(int G, const do
   if (threadIdx.x == 0) result[blockIdx.x] = s;
 }
 
-// Two consecutive elements per thread (16-byte loads).
+// Two consecutive elements per thread (16-byte loads).  t, when not null: the
+// point the next forward difference is evaluated at, formed while the new basis
+// vector is in registers (a pass of its own took 12 us for 2.4 million values).
 __global__ __launch_bounds__(kBlock) void multi_axpy_kernel(size_t n, int nv, const double *V,
                                                             size_t vstride, const double *coef,
                                                             double alpha, const double *w,
-                                                            double scale, double *out) {
+                                                            double scale, double *out, const double *y,
+                                                            double e, double *t) {
   const size_t stride = 2 * (size_t)gridDim.x * blockDim.x;
   for (size_t i = 2 * ((size_t)blockIdx.x * blockDim.x + threadIdx.x); i < n; i += stride) {
     if (i + 1 < n) {
@@ -166,20 +169,81 @@ __global__ __launch_bounds__(kBlock) void multi_axpy_kernel(size_t n, int nv, co
       r.x = scale * (wi.x + alpha * s0);
       r.y = scale * (wi.y + alpha * s1);
       *reinterpret_cast<double2 *>(out + i) = r;
+      if (t) {
+        const double2 yi = *reinterpret_cast<const double2 *>(y + i);
+        double2 ti;
+        ti.x = yi.x + e * r.x;
+        ti.y = yi.y + e * r.y;
+        *reinterpret_cast<double2 *>(t + i) = ti;
+      }
     } else {
       double s0 = 0.0;
       for (int k = 0; k < nv; ++k) s0 += coef[k] * V[(size_t)k * vstride + i];
-      out[i] = scale * (w[i] + alpha * s0);
+      const double r = scale * (w[i] + alpha * s0);
+      out[i] = r;
+      if (t) t[i] = y[i] + e * r;
     }
   }
 }
 
+// The second Gram-Schmidt pass's projections in one read of the basis: w loses
+// its components along the V_k, and the products of what is left with them and
+// itself are summed while both are in registers.  Bound by the nv + 2 streams; an
+// update and a product of their own would read the basis and w twice.
+template <int NV>
+__global__ __launch_bounds__(kBlock) void multi_orth_kernel(size_t n, const double *V, size_t vstride,
+                                                            const double *coef, double *w, double *partial) {
+  __shared__ double red[kBlock / 64];
+  const int G = gridDim.x;
+  double acc[NV + 1], c[NV];
+#pragma unroll
+  for (int k = 0; k <= NV; ++k) acc[k] = 0.0;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) c[k] = coef[k];
+  const size_t stride = 2 * (size_t)G * kBlock;
+  for (size_t i = 2 * ((size_t)blockIdx.x * kBlock + threadIdx.x); i < n; i += stride) {
+    if (i + 1 < n) {
+      double2 v[NV];
+#pragma unroll
+      for (int k = 0; k < NV; ++k) v[k] = *reinterpret_cast<const double2 *>(V + (size_t)k * vstride + i);
+      double2 wi = *reinterpret_cast<const double2 *>(w + i);
+      double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        s0 += c[k] * v[k].x;
+        s1 += c[k] * v[k].y;
+      }
+      wi.x -= s0;
+      wi.y -= s1;
+      *reinterpret_cast<double2 *>(w + i) = wi;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) acc[k] += v[k].x * wi.x + v[k].y * wi.y;
+      acc[NV] += wi.x * wi.x + wi.y * wi.y;
+    } else {
+      double s0 = 0.0;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) s0 += c[k] * V[(size_t)k * vstride + i];
+      const double wi = w[i] - s0;
+      w[i] = wi;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) acc[k] += V[(size_t)k * vstride + i] * wi;
+      acc[NV] += wi * wi;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k <= NV; ++k) {
+    const double s = block_sum(acc[k], red);
+    if (threadIdx.x == 0) partial[(size_t)k * G + blockIdx.x] = s;
+  }
+}
+
 // The FP32-basis form, two consecutive elements per thread (float2 basis
-// loads); out32 (optional) receives out rounded to FP32.
+// loads); out32 (optional) receives out rounded to FP32, t (optional) y + e out32.
 __global__ __launch_bounds__(kBlock) void multi_axpy32_kernel(size_t n, int nv, const float *V,
                                                               size_t vstride, const double *coef,
                                                               double alpha, const double *w,
-                                                              double scale, double *out, float *out32) {
+                                                              double scale, double *out, float *out32,
+                                                              const double *y, double e, double *t) {
   const size_t stride = 2 * (size_t)gridDim.x * blockDim.x;
   for (size_t i = 2 * ((size_t)blockIdx.x * blockDim.x + threadIdx.x); i < n; i += stride) {
     if (i + 1 < n) {
@@ -199,6 +263,13 @@ __global__ __launch_bounds__(kBlock) void multi_axpy32_kernel(size_t n, int nv, 
         r32.x = (float)r.x;
         r32.y = (float)r.y;
         *reinterpret_cast<float2 *>(out32 + i) = r32;
+        if (t) {
+          const double2 yi = *reinterpret_cast<const double2 *>(y + i);
+          double2 ti;
+          ti.x = yi.x + e * (double)r32.x;
+          ti.y = yi.y + e * (double)r32.y;
+          *reinterpret_cast<double2 *>(t + i) = ti;
+        }
       }
     } else {
       double s0 = 0.0;
@@ -206,6 +277,7 @@ __global__ __launch_bounds__(kBlock) void multi_axpy32_kernel(size_t n, int nv, 
       const double r = scale * (w[i] + alpha * s0);
       out[i] = r;
       if (out32) out32[i] = (float)r;
+      if (out32 && t) t[i] = y[i] + e * (double)(float)r;
     }
   }
 }
@@ -251,11 +323,32 @@ hipError_t launch_multi_dot(size_t n, int nv, const double *V, size_t vstride, c
 
 hipError_t launch_multi_axpy(size_t n, int nv, const double *V, size_t vstride, const double *coef,
                              double alpha, const double *w, double scale, double *out,
-                             hipStream_t st) {
+                             hipStream_t st, const double *y, double e, double *t) {
   if (nv < 0 || nv > kMaxBasis) return hipErrorInvalidValue;
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(multi_axpy_kernel, dim3(stream_blocks((n + 1) / 2)), dim3(kBlock), 0, st, n, nv,
-                     V, vstride, coef, alpha, w, scale, out);
+                     V, vstride, coef, alpha, w, scale, out, y, e, t);
+  return hipGetLastError();
+}
+
+hipError_t launch_multi_orth(size_t n, int nv, const double *V, size_t vstride, const double *coef, double *w,
+                             double *scratch, double *result, hipStream_t st) {
+  if (nv < 1 || nv > kOrthBasis) return hipErrorInvalidValue;
+  const int G = dot_groups((n + 1) / 2);  // within multi_dot_scratch(n, nv + 1)
+  const dim3 grid((unsigned)G), block(kBlock);
+  switch (nv) {
+    case 1: hipLaunchKernelGGL(multi_orth_kernel<1>, grid, block, 0, st, n, V, vstride, coef, w, scratch); break;
+    case 2: hipLaunchKernelGGL(multi_orth_kernel<2>, grid, block, 0, st, n, V, vstride, coef, w, scratch); break;
+    case 3: hipLaunchKernelGGL(multi_orth_kernel<3>, grid, block, 0, st, n, V, vstride, coef, w, scratch); break;
+    case 4: hipLaunchKernelGGL(multi_orth_kernel<4>, grid, block, 0, st, n, V, vstride, coef, w, scratch); break;
+    case 5: hipLaunchKernelGGL(multi_orth_kernel<5>, grid, block, 0, st, n, V, vstride, coef, w, scratch); break;
+    case 6: hipLaunchKernelGGL(multi_orth_kernel<6>, grid, block, 0, st, n, V, vstride, coef, w, scratch); break;
+    case 7: hipLaunchKernelGGL(multi_orth_kernel<7>, grid, block, 0, st, n, V, vstride, coef, w, scratch); break;
+    default: hipLaunchKernelGGL(multi_orth_kernel<8>, grid, block, 0, st, n, V, vstride, coef, w, scratch); break;
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(multi_dot_final_kernel, dim3((unsigned)nv + 1), dim3(kBlock), 0, st, G, scratch, result);
   return hipGetLastError();
 }
 
@@ -286,11 +379,11 @@ hipError_t launch_multi_dot32(size_t n, int nv, const float *V, size_t vstride, 
 
 hipError_t launch_multi_axpy32(size_t n, int nv, const float *V, size_t vstride, const double *coef,
                                double alpha, const double *w, double scale, double *out, float *out32,
-                               hipStream_t st) {
+                               hipStream_t st, const double *y, double e, double *t) {
   if (nv < 0 || nv > kMaxBasis) return hipErrorInvalidValue;
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(multi_axpy32_kernel, dim3(stream_blocks((n + 1) / 2)), dim3(kBlock), 0, st, n, nv,
-                     V, vstride, coef, alpha, w, scale, out, out32);
+                     V, vstride, coef, alpha, w, scale, out, out32, y, e, t);
   return hipGetLastError();
 }
 

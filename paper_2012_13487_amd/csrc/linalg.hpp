@@ -29,10 +29,18 @@ hipError_t launch_multi_dot(size_t n, int nv, const double *V, size_t stride, co
                             double *scratch, double *result, hipStream_t stream);
 
 // out = scale (w + alpha sum_{k < nv} coef[k] V_k), coef in device memory
-// (nv <= kMaxBasis); out may alias w.
+// (nv <= kMaxBasis); out may alias w.  t, when not null, receives y + e out.
 hipError_t launch_multi_axpy(size_t n, int nv, const double *V, size_t stride, const double *coef,
                              double alpha, const double *w, double scale, double *out,
-                             hipStream_t stream);
+                             hipStream_t stream, const double *y = nullptr, double e = 0.0,
+                             double *t = nullptr);
+
+// w -= sum_{k < nv} coef[k] V_k, then result[k] = V_k . w for k < nv and
+// result[nv] = w . w, for 1 <= nv <= kOrthBasis; w is none of the V_k.  scratch
+// as for launch_multi_dot(n, nv + 1).
+constexpr int kOrthBasis = 8;
+hipError_t launch_multi_orth(size_t n, int nv, const double *V, size_t stride, const double *coef, double *w,
+                             double *scratch, double *result, hipStream_t stream);
 
 // The same operations with the Krylov basis V stored in FP32 (w, coef and
 // out stay FP64).  lincomb_mixed: out = a x + b y + c z with y in FP32.
@@ -45,9 +53,11 @@ hipError_t launch_multi_dot32(size_t n, int nv, const float *V, size_t stride, c
                               double *scratch, double *result, hipStream_t stream);
 
 // out = scale (w + alpha sum_{k < nv} coef[k] V_k); out32, when not null,
-// receives out rounded to FP32.  out may alias w.
+// receives out rounded to FP32, and t, when neither is null, y + e out32.  out
+// may alias w.
 hipError_t launch_multi_axpy32(size_t n, int nv, const float *V, size_t stride, const double *coef,
                                double alpha, const double *w, double scale, double *out,
-                               float *out32, hipStream_t stream);
+                               float *out32, hipStream_t stream, const double *y = nullptr, double e = 0.0,
+                               double *t = nullptr);
 
 }  // namespace dgbgk

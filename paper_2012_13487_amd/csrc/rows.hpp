@@ -12,6 +12,7 @@ namespace dgbgk {
 
 constexpr int kRowMaxN1 = 5;
 constexpr int kRateSums = 5;  // the stage of launch_rows that reduces the moment rates of L(f_s) only
+constexpr int kJacobian = 6;  // FP64: out = fn + c_out (L(f_s) - f1)
 constexpr int kRowMaxP = 4;  // a row's values and rates live in registers
 constexpr int kRowStripMin = 1024;  // work-groups from which their order matters to the caches
 constexpr int kRowMinQ = 8;  // fewer velocities leave most lanes of a wavefront without a row
@@ -118,7 +119,7 @@ struct RowArgs {
   double mconst[7];
   double resid_scale;  // kRateSums: the largest scaled moment rate goes to *result (one velocity tile), or the
   unsigned long long *result;  // sums to pout (several; launch_rate_max)
-  int stage;           // 0: out = L(f_s); 1..4: classical RK4 stage; kRateSums
+  int stage;           // 0: out = L(f_s); 1..4: classical RK4 stage; kRateSums; kJacobian
 };
 
 // The plan for a problem of order p with Q velocities and K elements; value

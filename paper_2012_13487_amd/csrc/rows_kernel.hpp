@@ -304,17 +304,20 @@ __device__ __forceinline__ void row_result(const RowArgs<float> &, const float (
 // FP64, classical RK4 from the stage states (f_1 - f_n = dt/2 k_1, f_2 - f_n =
 // dt/2 k_2, f_3 - f_n = dt k_3), so that no accumulator is written: 16, 24, 24
 // and 40 bytes per value in stages 1 to 4.
-//   MODE 0: o = k (kRateSums: o is summed, not stored)
+//   MODE 0: o = k (kRateSums: o is summed, not stored)      kJacobian: o = x + c (k - y)
 //   MODE 1: o = kv = f_n + dt/2 k      2: o = x + c k  (x = f_n)
 //   MODE 4: o = x + [(y - x) + 2 (z - x) + (kv - x)] / 3, kv = f_3 + dt/2 k  (x = f_n, y = f_1,
 //           z = f_2; the differences are small, so the state is rounded once)
 // FP32, increment form (the state is rounded once per step): d = sum b_i dt k_i
 //   MODE 1: d = dt/6 k, o = x + dt/2 k      2: d += c k, o = x + c' k      4: o = x + (d + dt/6 k)
+// Whether a mode hands on the sums of its outputs (kind 1).
+constexpr bool row_sums_mode(int mode) { return mode != 0 && mode != kJacobian; }
+
 template <typename T, int MODE>
 struct Streams {
   static constexpr bool F64 = sizeof(T) == 8;
-  static constexpr bool X = F64 ? (MODE == 2 || MODE == 4) : MODE != 0 && MODE != kRateSums;
-  static constexpr bool Y = F64 ? MODE == 4 : (MODE == 2 || MODE == 4);
+  static constexpr bool X = F64 ? (MODE == 2 || MODE == 4 || MODE == kJacobian) : MODE != 0 && MODE != kRateSums;
+  static constexpr bool Y = F64 ? (MODE == 4 || MODE == kJacobian) : (MODE == 2 || MODE == 4);
   static constexpr bool Z = F64 && MODE == 4;
   static constexpr bool ACC = !F64 && (MODE == 1 || MODE == 2);
 };
@@ -322,6 +325,7 @@ template <int MODE>
 __device__ __forceinline__ double update_value(double kv, double x, double y, double z, double,
                                                double co, double &) {
   if (MODE == 2) return x + co * kv;
+  if (MODE == kJacobian) return x + co * (kv - y);
   if (MODE == 4) return x + ((y - x) + 2.0 * (z - x) + (kv - x)) * (1.0 / 3.0);
   return kv;
 }
@@ -479,25 +483,28 @@ __device__ __forceinline__ double wall_sum(const A &a, const T *tile, int lo, in
 }
 
 // Loads of a wavefront's rows [r0, r0 + 64) counted from `base` (16-byte
-// aligned) into registers, and from there into the tile.
+// aligned) into registers, and from there into the tile.  Beyond nrows the last
+// access is repeated (those rows are never read): with a branch per access
+// instead, the sums of p = 3 took 214 registers, now 67, and problems with
+// ragged wavefronts were 1 to 2% slower.
 template <int P, typename T, typename V, int N>
 __device__ __forceinline__ void tile_load(V (&v)[N], const T *base, int nrows, int lane) {
   using Sh = RowShape<P, T>;
   const int nacc = (nrows * Sh::NP + Sh::VW - 1) / Sh::VW;
 #pragma unroll
   for (int u = 0; u < Sh::NLD; ++u) {
-    const int c = lane + 64 * u;
-    if (c < nacc) v[u] = ld_stream<false, V>(base, 16u * c);
+    const int c = min(lane + 64 * u, nacc - 1);
+    v[u] = ld_stream<false, V>(base, 16u * c);
   }
 }
 template <int P, typename T, typename V, int N>
-__device__ __forceinline__ void tile_store(const V (&v)[N], T *tile, int nrows, int lane) {
+__device__ __forceinline__ void tile_store(const V (&v)[N], T *tile, int lane) {
   using Sh = RowShape<P, T>;
-  const int nacc = (nrows * Sh::NP + Sh::VW - 1) / Sh::VW;
+  constexpr int most = 64 * Sh::NP / Sh::VW;
 #pragma unroll
   for (int u = 0; u < Sh::NLD; ++u) {
     const int c = lane + 64 * u;
-    if (c >= nacc) continue;
+    if (64 * u + 63 >= most && c >= most) continue;
     if constexpr (Sh::LIN) {
       *reinterpret_cast<V *>(tile + Sh::VW * c) = v[u];
     } else {
@@ -870,7 +877,7 @@ __device__ __forceinline__ void rows_element(const A &a, int k, int vt, int wave
     }
   }
   if (work) {
-    tile_store<P, T>(v, tile, hi, lane);
+    tile_store<P, T>(v, tile, lane);
     ev[lane] = d2{in.cxd, in.cyd};
   }
   __syncthreads();
@@ -882,14 +889,14 @@ __device__ __forceinline__ void rows_element(const A &a, int k, int vt, int wave
     if (wall) row_walls<P, T, REF>(a, q, rw, in);
     if (lane >= lo && lane < hi) row_phase<P, T, MODE, REF>(a, tile, lane, in, mom);
     wave_sync();
-    constexpr bool SUM = MODE != 0, WALLS = SUM && MODE != kRateSums;
+    constexpr bool SUM = row_sums_mode(MODE), WALLS = SUM && MODE != kRateSums;
     rows_update<P, T, MODE, REF, SUM>(a, tile, ev, off, lo, hi, lane, WALLS && wall, cs);
     if (WALLS && wall) {
       wave_sync();
       ws = wall_sum<P, T>(a, tile, lo, hi, q0, lane, nbr);
     }
   }
-  if constexpr (MODE == 0) return;
+  if constexpr (!row_sums_mode(MODE)) return;
   double *po = a.pout + ((size_t)vt * a.K + k) * 7 * NP;
   if constexpr (MODE == kRateSums)
     rows_sums_out<P, T, true>(cs, ws, false, wave, lane, nw, on, nbr, lds, red, po, a.resid_scale,
@@ -900,16 +907,19 @@ __device__ __forceinline__ void rows_element(const A &a, int k, int vt, int wave
 
 // The same sums of a state as it is (after it was set from outside a step), by
 // the same lanes in the same order, so that a state read out and set again
-// continues bit for bit.
+// continues bit for bit.  Bound by the one read; summed by the update's pass
+// with its velocities in LDS (read from memory in the loop, 2.4 million FP64
+// values took 15.4 us, now 6.7).
 template <int P, typename T, typename A>
 __device__ __forceinline__ void rows_state_sums(const A &a, int k, int vt, char *lds) {
   using Sh = RowShape<P, T>;
   using V = typename VecOf<T>::type;
-  constexpr int NP = Sh::NP, VW = Sh::VW, PR = Sh::PR;
+  constexpr int NP = Sh::NP, PR = Sh::PR;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int nw = a.nw, Q = a.Q;
-  constexpr int WB = row_wave_bytes(NP, sizeof(T)) + 64 * 16;
+  constexpr int TB = row_wave_bytes(NP, sizeof(T)), WB = TB + 64 * 16;
   T *tile = reinterpret_cast<T *>(lds + wave * WB);
+  d2 *ev = reinterpret_cast<d2 *>(lds + wave * WB + TB);
   double *red = reinterpret_cast<double *>(lds + nw * WB);
   const int ey = quotient(k, a.dnx), ex = k - ey * a.nx;
   const int nbr[4] = {row_neighbour(ex, ey, k, 0, a), row_neighbour(ex, ey, k, 1, a),
@@ -922,32 +932,17 @@ __device__ __forceinline__ void rows_state_sums(const A &a, int k, int vt, char 
   ColumnSums<T> cs;
   cs.clear();
   double ws = 0.0;
-  const int g = lane / Sh::RA, w = lane - g * Sh::RA;
-  const int r1 = (VW * w) / NP, r2 = (VW * w + VW - 1) / NP;
-  const int cross = r2 > r1 ? r2 * NP - VW * w : VW;
   const int c = vt * nw + wave;
   if (c < nch) {
     const int lo = max(0, lead - 64 * c), hi = min(64, vrows - 64 * c), q0 = 64 * c - lead;
     V v[Sh::NLD];
     tile_load<P, T>(v, a.fs + base + (ptrdiff_t)c * 64 * NP, hi, lane);
+    const int q = min(max(q0 + lane, 0), Q - 1);
+    ev[lane] = d2{a.vel[q], a.vel[Q + q]};
     wave_sync();
-    tile_store<P, T>(v, tile, hi, lane);
+    tile_store<P, T>(v, tile, lane);
     wave_sync();
-    if (g < Sh::G)
-      for (int it = 0; it * Sh::RPI < hi; ++it) {
-        const int rb = PR * (g + Sh::G * it);
-        if (!(rb + r2 >= lo && rb + r1 < hi)) continue;
-        const bool first = rb + r1 >= lo && rb + r1 < hi, last = rb + r2 >= lo && rb + r2 < hi;
-        const int qa = max(q0 + rb + r1, 0), qb = min(q0 + rb + r2, Q - 1);
-        const V o = *reinterpret_cast<const V *>(Sh::LIN ? tile + rb * NP + VW * w : tile + Sh::at(rb, VW * w));
-#pragma unroll
-        for (int j = 0; j < VW; ++j) {
-          const bool in1 = PR == 1 || j < cross;
-          const double oj = (in1 ? first : last) ? (double)o[j] : 0.0;
-          const int q = in1 ? qa : qb;
-          cs.add(j, oj, a.vel[q], a.vel[Q + q]);
-        }
-      }
+    rows_update<P, T, kRateSums, false, true>(a, tile, ev, base + (ptrdiff_t)c * 64 * NP, lo, hi, lane, false, cs);
     if (wall) ws += wall_sum<P, T>(a, tile, lo, hi, q0, lane, nbr);
   }
   rows_sums_out<P, T>(cs, ws, wall, wave, lane, nw, true, nbr, lds, red,
@@ -984,7 +979,7 @@ __device__ __forceinline__ void rows_wave(const A &a, int w, char *lds) {
   tile_load<P, T>(v, a.fs + base, hi, lane);
   row_traces_load<P, T>(a, kr, q, row_neighbour(exr, eyr, kr, 3, a), row_neighbour(exr, eyr, kr, 1, a),
                         row_neighbour(exr, eyr, kr, 0, a), row_neighbour(exr, eyr, kr, 2, a), in);
-  tile_store<P, T>(v, tile, hi, lane);
+  tile_store<P, T>(v, tile, lane);
   ev[lane] = d2{in.cxd, in.cyd};
   wave_sync();
 
@@ -1228,6 +1223,8 @@ hipError_t launch_stage_of(int stage, const A &a, size_t lds, hipStream_t st) {
     case 3: return launch_one<KIND, P, T, 2, REF>(a, lds, st);
     case 4: return launch_one<KIND, P, T, 4, REF>(a, lds, st);
     case kRateSums: return launch_one<KIND, P, T, kRateSums, REF>(a, lds, st);
+    case kJacobian:
+      if constexpr (sizeof(T) == 8) return launch_one<KIND, P, T, kJacobian, REF>(a, lds, st);
     default: return hipErrorInvalidValue;
   }
 }

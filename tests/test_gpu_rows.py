@@ -132,6 +132,44 @@ def test_residual_matches_the_rates_block_kernels_write(p, q, prec):
         assert e.value.code == binding.ENONFINITE
 
 
+@pytest.mark.parametrize("fp32_basis", [False, True], ids=["basis64", "basis32"])
+@pytest.mark.parametrize("p,q,nx,ny,walls,mult,restart",
+                         [(1, 9, 1, 1, "box", 10, 30), (2, 9, 3, 1, "cavity", 100, 5), (3, 15, 5, 3, "couette", 10, 30),
+                          (4, 31, 3, 3, "cavity", 30, 64), (1, 65, 3, 3, "cavity", 100, 1), (2, 62, 3, 3, "cavity", 10, 30),
+                          (2, 257, 3, 2, "couette", 30, 12), (3, 65, 2, 3, "box", 10, 30), (4, 321, 2, 2, "cavity", 10, 30)])
+def test_implicit_step_by_row_kernels_solves_its_equation(oracle_mod, p, q, nx, ny, walls, mult, restart, fp32_basis):
+    """A backward-Euler step with its products by the row kernels (odd lengths,
+    one to several velocity tiles, second Gram-Schmidt passes, short and long
+    cycles): y - f - dt L(y) with the oracle's L.  Newton stops at 1e-13 of the
+    first residual in the 2-norm, at most 1e-13 sqrt(n) < 2e-11 in the maximum
+    norm; the bar leaves the rest to the rounding of L."""
+    spec = _spec(p, q, nx, ny, walls)
+    print(f"[gpu] implicit rows {spec.name} x{mult} restart {restart} fp32 basis {fp32_basis}", flush=True)
+    g, o = binding.Solver.from_spec(spec), oracle_mod.Oracle.from_spec(spec)
+    f = workloads.perturbed_state(5 + q, o.w, o.K, o.Np, amp=0.15)
+    dt = mult * o.stable_dt(0.2)
+    g.set_state(f)
+    r0 = g.residual()
+    opt = dict(newton_rtol=1e-13, newton_atol=1e-17, max_newton=4 if mult == 100 else 60,
+               krylov_rtol=1e-5 if fp32_basis else 1e-8, max_krylov=1000, restart=restart, krylov_fp32=fp32_basis)
+    rep = g.implicit_step(1, dt, "backward_euler", **opt)
+    y = g.get_state()
+    if mult == 100:  # (cycles this short stagnate at this step, with the block kernels' products as well)
+        b = binding.Solver.from_spec(spec)
+        b.set_block_elements(1)
+        b.set_state(f)
+        blocks = b.implicit_step(1, dt, "backward_euler", **opt)
+        for name in ("converged", "newton_iterations", "krylov_iterations", "rhs_evaluations"):
+            assert rep[name] == blocks[name], (rep, blocks)
+    else:
+        assert rep["converged"] == 1, rep
+        F = y - f - dt * o.rhs(y)
+        assert np.max(np.abs(F)) < 1e-10 * np.max(np.abs(dt * o.rhs(f)))
+    h = binding.Solver.from_spec(spec)  # (the sums of f_n that a residual left behind are not the new state's)
+    h.set_state(y)
+    assert h.residual() == g.residual() and r0 > 0
+
+
 def test_block_elements_and_tiles_choose_the_block_kernels(oracle_mod):
     """A block size or a velocity tile set by the caller keeps the block kernels
     (rounding apart from the automatic row kernels), back to automatic the row
