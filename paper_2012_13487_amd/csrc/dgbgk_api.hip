@@ -20,6 +20,7 @@
 #include "init.hpp"
 #include "kernels32.hpp"
 #include "linalg.hpp"
+#include "moments.hpp"
 #include "rows.hpp"
 
 using namespace dgbgk;
@@ -670,8 +671,8 @@ int ref_refresh(dgbgk_solver *s) {
   e = launch_stage(s->p, a, c.lds, c.ntiles, s->stream);
   if (e == hipSuccess) e = launch_f64_to_f32(s->d_xfer, s->g_rref, n, s->stream);
   if (e == hipSuccess)
-    e = launch_moments(s->d_fref, s->d_vel, K, s->p, s->Q, s->pb.nx, s->pb.ny, 0, s->wall_den_inv,
-                       s->d_mref, s->d_mref + KN, s->d_mref + 2 * KN, nullptr, s->stream);
+    e = launch_node_moments(s->d_fref, nullptr, 0.0, s->d_vel, K, s->Np, s->Q, s->d_mref, s->d_mref + KN,
+                            s->d_mref + 2 * KN, s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "reference right-hand side");
   return DGBGK_OK;
 }
@@ -1432,20 +1433,10 @@ int dgbgk_moments(dgbgk_solver *s, double *rho, double *ux, double *uy) {
   if (!s->have_state) return fail(s, DGBGK_ESTATE, "no state: call init or set_state first");
   const size_t KN = (size_t)s->K * s->Np;
   hipError_t e = hipSuccess;
-  if (is_ref(s->prec)) {  // f = f_ref + g in FP64 (transfer buffer), then the FP64 moments
-    e = launch_ref_sum(s->d_fref, s->g_fn, s->d_xfer, KN * s->Q, s->stream);
-    if (e == hipSuccess)
-      e = launch_moments(s->d_xfer, s->d_vel, (int)s->K, s->p, s->Q, s->pb.nx, s->pb.ny, 0,
-                         s->wall_den_inv, s->d_mom, s->d_mom + KN, s->d_mom + 2 * KN, nullptr,
-                         s->stream);
-  } else
-    e =
-      is_fp32(s->prec)
-          ? launch_moments32(s->g_fn, s->d_vel, (int)s->K, s->Np, s->Q, s->rho_ref, s->d_mom,
-                             s->d_mom + KN, s->d_mom + 2 * KN, s->stream)
-          : launch_moments(s->d_fn, s->d_vel, (int)s->K, s->p, s->Q, s->pb.nx, s->pb.ny, 0,
-                           s->wall_den_inv, s->d_mom, s->d_mom + KN, s->d_mom + 2 * KN, nullptr,
-                           s->stream);
+  const bool f32 = is_fp32(s->prec), ref = is_ref(s->prec);
+  e = launch_node_moments(ref ? s->d_fref : f32 ? nullptr : s->d_fn, f32 ? s->g_fn : nullptr,
+                          f32 && !ref ? s->rho_ref : 0.0, s->d_vel, (int)s->K, s->Np, s->Q, s->d_mom,
+                          s->d_mom + KN, s->d_mom + 2 * KN, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(rho, s->d_mom, KN * sizeof(double), hipMemcpyDeviceToHost, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(ux, s->d_mom + KN, KN * sizeof(double), hipMemcpyDeviceToHost, s->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(uy, s->d_mom + 2 * KN, KN * sizeof(double), hipMemcpyDeviceToHost, s->stream);

@@ -856,25 +856,6 @@ __global__ void init_equilibrium32_kernel(float *g, const double *vel, size_t KN
   g[((i / Np) * Q + q) * Np + i % Np] = (float)(feq - w * rho_ref);
 }
 
-__global__ __launch_bounds__(256) void moments32_kernel(const float *g, const double *vel, size_t KNP,
-                                                        int Np, int Q, double rho_ref, double *rho,
-                                                        double *ux, double *uy) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= KNP) return;
-  const size_t k = i / Np, n = i % Np;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int q = 0; q < Q; ++q) {
-    const double cx = vel[q], cy = vel[Q + q], w = vel[2 * Q + q];
-    const double v = (double)g[(k * Q + q) * Np + n] + w * rho_ref;
-    s0 += v;
-    s1 += cx * v;
-    s2 += cy * v;
-  }
-  if (rho) rho[i] = s0;
-  if (ux) ux[i] = s1 / s0;
-  if (uy) uy[i] = s2 / s0;
-}
-
 // Reference form: f_r += g, g = 0 (both element-major).
 __global__ __launch_bounds__(256) void ref_fold_kernel(double *fref, float *g, size_t n) {
   const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -888,13 +869,6 @@ __global__ __launch_bounds__(256) void f64_to_f32_kernel(const double *src, floa
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
     dst[i] = (float)src[i];
-}
-
-__global__ __launch_bounds__(256) void ref_sum_kernel(const double *fref, const float *g, double *dst,
-                                                      size_t n) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-    dst[i] = fref[i] + (double)g[i];
 }
 
 // host order [q][k][n] <-> element-major [k][q][n]
@@ -1148,10 +1122,6 @@ hipError_t launch_f64_to_f32(const double *src, float *dst, size_t n, hipStream_
   return launch_stream_kernel(f64_to_f32_kernel, n, st, src, dst);
 }
 
-hipError_t launch_ref_sum(const double *fref, const float *g, double *dst, size_t n, hipStream_t st) {
-  return launch_stream_kernel(ref_sum_kernel, n, st, fref, g, dst);
-}
-
 hipError_t launch_from_ref(const double *fref, const float *g, double *dst, int K, int Np, int Q,
                            hipStream_t st) {
   const size_t KNP = (size_t)K * Np;
@@ -1199,14 +1169,6 @@ hipError_t launch_moment_rows32(const float *g, const double *vel, int K, int Np
   const size_t KNP = (size_t)K * Np;
   hipLaunchKernelGGL(moment_rows32_kernel, dim3((unsigned)((KNP + 255) / 256)), dim3(256), 0, st, g,
                      vel, K, Np, Q, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_moments32(const float *g, const double *vel, int K, int Np, int Q, double rho_ref,
-                            double *rho, double *ux, double *uy, hipStream_t st) {
-  const size_t KNP = (size_t)K * Np;
-  hipLaunchKernelGGL(moments32_kernel, dim3((unsigned)((KNP + 255) / 256)), dim3(256), 0, st, g,
-                     vel, KNP, Np, Q, rho_ref, rho, ux, uy);
   return hipGetLastError();
 }
 

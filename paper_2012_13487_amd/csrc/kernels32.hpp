@@ -75,13 +75,11 @@ hipError_t launch_batch_stage32(int p, int stage, int cw, int contract, int ref,
                                 size_t lds_bytes, int groups, hipStream_t stream);
 
 // Reference form helpers (element-major arrays of n = K Np Q values):
-// fold: f_r += g, g = 0;  to_f32: dst = (float) src;  sum: dst = f_r + g;
+// fold: f_r += g, g = 0;  to_f32: dst = (float) src;
 // from_ref: dst[q][k][n] (host order) = f_r + g;  to_ref: g = src (host
 // order) - f_r.
 hipError_t launch_ref_fold(double *fref, float *g, size_t n, hipStream_t stream);
 hipError_t launch_f64_to_f32(const double *src, float *dst, size_t n, hipStream_t stream);
-hipError_t launch_ref_sum(const double *fref, const float *g, double *dst, size_t n,
-                          hipStream_t stream);
 hipError_t launch_from_ref(const double *fref, const float *g, double *dst, int K, int Np, int Q,
                            hipStream_t stream);
 hipError_t launch_to_ref(const double *src, const double *fref, float *g, int K, int Np, int Q,
@@ -98,10 +96,6 @@ hipError_t launch_from_dev32(const float *src, double *dst, const double *vel, i
 hipError_t launch_init_equilibrium32(float *g, const double *vel, int K, int Np, int Q, double rho0,
                                      double ux0, double uy0, double theta, double rho_ref,
                                      hipStream_t stream);
-
-// rho, ux, uy of f = g + w rho_ref at every node (FP64 sums).
-hipError_t launch_moments32(const float *g, const double *vel, int K, int Np, int Q,
-                            double rho_ref, double *rho, double *ux, double *uy, hipStream_t stream);
 
 // Moment rows of an FP32 state g (element-major): out[k][7][Np] = sum over
 // velocities of (1, e_x, e_y, outgoing normal speed at the bottom, right,
