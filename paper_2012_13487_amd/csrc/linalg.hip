@@ -138,13 +138,16 @@ __global__ __launch_bounds__(kBlock) void multi_dot32_partial_kernel(size_t n, i
 
 // Work-group k sums the G partials of vector k in a fixed order.
 __global__ __launch_bounds__(kBlock) void multi_dot_final_kernel(int G, const double *partial,
-                                                                 double *result) {
+                                                                 double *result, double *host) {
   __shared__ double red[kBlock / 64];
   const double *p = partial + (size_t)blockIdx.x * G;
   double acc = 0.0;
   for (int g = threadIdx.x; g < G; g += kBlock) acc += p[g];
   const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) result[blockIdx.x] = s;
+  if (threadIdx.x == 0) {
+    result[blockIdx.x] = s;
+    if (host) host[blockIdx.x] = s;
+  }
 }
 
 // Two consecutive elements per thread (16-byte loads).  t, when not null: the
@@ -154,7 +157,8 @@ __global__ __launch_bounds__(kBlock) void multi_axpy_kernel(size_t n, int nv, co
                                                             size_t vstride, const double *coef,
                                                             double alpha, const double *w,
                                                             double scale, double *out, const double *y,
-                                                            double e, double *t) {
+                                                            double e, double *t, int pass) {
+  if (pass) scale = orth_scale(pass, nv, coef);
   const size_t stride = 2 * (size_t)gridDim.x * blockDim.x;
   for (size_t i = 2 * ((size_t)blockIdx.x * blockDim.x + threadIdx.x); i < n; i += stride) {
     if (i + 1 < n) {
@@ -308,7 +312,7 @@ hipError_t launch_lincomb(size_t n, double a, const double *x, double b, const d
 size_t multi_dot_scratch(size_t n, int nv) { return (size_t)dot_groups(n) * (size_t)nv; }
 
 hipError_t launch_multi_dot(size_t n, int nv, const double *V, size_t vstride, const double *w,
-                            double *scratch, double *result, hipStream_t st) {
+                            double *scratch, double *result, hipStream_t st, double *host) {
   if (nv < 1 || nv > kMaxBasis) return hipErrorInvalidValue;
   const int G = dot_groups((n + 1) / 2);  // within multi_dot_scratch(n, nv)
   const unsigned gy = (unsigned)((nv + kVecs - 1) / kVecs);
@@ -317,7 +321,7 @@ hipError_t launch_multi_dot(size_t n, int nv, const double *V, size_t vstride, c
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(multi_dot_final_kernel, dim3((unsigned)nv), dim3(kBlock), 0, st, G, scratch,
-                     result);
+                     result, host);
   return hipGetLastError();
 }
 
@@ -327,12 +331,21 @@ hipError_t launch_multi_axpy(size_t n, int nv, const double *V, size_t vstride, 
   if (nv < 0 || nv > kMaxBasis) return hipErrorInvalidValue;
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(multi_axpy_kernel, dim3(stream_blocks((n + 1) / 2)), dim3(kBlock), 0, st, n, nv,
-                     V, vstride, coef, alpha, w, scale, out, y, e, t);
+                     V, vstride, coef, alpha, w, scale, out, y, e, t, 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_multi_orth_scaled(size_t n, int pass, int nv, const double *V, size_t vstride, const double *h,
+                                    double *w, hipStream_t st, const double *y, double e, double *t) {
+  if (nv < 1 || nv > kMaxBasis) return hipErrorInvalidValue;
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(multi_axpy_kernel, dim3(stream_blocks((n + 1) / 2)), dim3(kBlock), 0, st, n, nv,
+                     V, vstride, h, -1.0, w, 1.0, w, y, e, t, pass);
   return hipGetLastError();
 }
 
 hipError_t launch_multi_orth(size_t n, int nv, const double *V, size_t vstride, const double *coef, double *w,
-                             double *scratch, double *result, hipStream_t st) {
+                             double *scratch, double *result, hipStream_t st, double *host) {
   if (nv < 1 || nv > kOrthBasis) return hipErrorInvalidValue;
   const int G = dot_groups((n + 1) / 2);  // within multi_dot_scratch(n, nv + 1)
   const dim3 grid((unsigned)G), block(kBlock);
@@ -348,7 +361,7 @@ hipError_t launch_multi_orth(size_t n, int nv, const double *V, size_t vstride, 
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(multi_dot_final_kernel, dim3((unsigned)nv + 1), dim3(kBlock), 0, st, G, scratch, result);
+  hipLaunchKernelGGL(multi_dot_final_kernel, dim3((unsigned)nv + 1), dim3(kBlock), 0, st, G, scratch, result, host);
   return hipGetLastError();
 }
 
@@ -373,7 +386,7 @@ hipError_t launch_multi_dot32(size_t n, int nv, const float *V, size_t vstride, 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(multi_dot_final_kernel, dim3((unsigned)nt), dim3(kBlock), 0, st, G, scratch,
-                     result);
+                     result, (double *)nullptr);
   return hipGetLastError();
 }
 
