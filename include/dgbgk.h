@@ -429,9 +429,9 @@ int dgbgk_batch_create(dgbgk_solver *const *solvers, int32_t n, void *hip_stream
                        dgbgk_batch **out);
 
 /* use_graph = k > 0: k RK4 steps of the batch are captured once in a hipGraph
- * and replayed (plus a one-step graph for the remainder of a call;
- * re-captured when the membership changes, not when dt does: the descriptors
- * are device data).  0: ordinary launches.  k in 0..1000. */
+ * and replayed (the remainder of a call, and the first k steps, are ordinary
+ * launches; re-captured when the membership changes, not when dt does: the
+ * descriptors are device data).  0: ordinary launches.  k in 0..1000. */
 int dgbgk_batch_set_graph(dgbgk_batch *b, int32_t use_graph);
 
 /* nsteps RK4 steps of every member; dt[i] is member i's time step (n values,

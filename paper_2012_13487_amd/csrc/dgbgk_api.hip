@@ -2319,7 +2319,7 @@ struct dgbgk_batch {
   std::vector<int> class_lane, solo_lane;
   int graph_steps = 0;                // RK4 steps per captured graph (0: eager)
   hipGraphExec_t exec = nullptr;      // graph_steps steps
-  hipGraphExec_t exec1 = nullptr;     // one step (the remainder of a call)
+  bool launched = false;              // a step ran eagerly (it sets the kernels' LDS attributes, outside a capture)
   size_t off_res = 0;                 // byte offset of the residual accumulators in dev
   std::vector<unsigned long long> res_host;
   std::string err;
@@ -2526,14 +2526,11 @@ int enqueue_steps(dgbgk_batch *b, int64_t nsteps) {
   return rc;
 }
 
-int enqueue_step(dgbgk_batch *b) { return enqueue_steps(b, 1); }
-
 void drop_graph(dgbgk_batch *b) {
-  if (b->exec || b->exec1) (void)hipStreamSynchronize(b->stream);  // replays in flight
-  if (b->exec && b->exec != b->exec1) (void)hipGraphExecDestroy(b->exec);
-  if (b->exec1) (void)hipGraphExecDestroy(b->exec1);
+  if (!b->exec) return;
+  (void)hipStreamSynchronize(b->stream);  // replays in flight
+  (void)hipGraphExecDestroy(b->exec);
   b->exec = nullptr;
-  b->exec1 = nullptr;
 }
 
 // Captures `steps` RK4 steps of the batch into *out.
@@ -2637,7 +2634,13 @@ int dgbgk_batch_create(dgbgk_solver *const *solvers, int32_t n, void *hip_stream
     c.lds = std::max(c.lds, rows ? row_item_lds(s->rows) : s->lds);
   }
   for (auto &c : b->cls)
-    if (c.rows) xcd_order(c.items);
+    if (c.rows) {
+      // the longer work-groups (an element over several wavefronts) start first
+      std::stable_sort(c.items.begin(), c.items.end(), [&](const int2 &x, const int2 &y) {
+        return b->s[c.members[x.x]]->rows.kind < b->s[c.members[y.x]]->rows.kind;
+      });
+      xcd_order(c.items);
+    }
   // device layout: per class its items, then its descriptors (5 stages x members)
   size_t off = 0;
   for (auto &c : b->cls) {
@@ -2766,28 +2769,19 @@ int dgbgk_batch_step(dgbgk_batch *b, int64_t nsteps, const double *dt) {
   if (nsteps == 0) return DGBGK_OK;
   if ((rc = batch_partials(b))) return rc;
   for (auto *s : b->s) s->part_valid = false;  // until every step is enqueued
+  // the steps beyond whole graphs run eagerly (so does a first graph's worth):
+  // as fast as replays of one step each, without a second graph
   const int k = b->graph_steps;
-  if (k > 0 && ((nsteps >= k && !b->exec) || (nsteps % k != 0 && !b->exec1))) {
-    // one eager step first: it sets the kernels' LDS attributes outside the capture
-    if ((rc = enqueue_step(b))) return rc;
-    --nsteps;
-    for (auto *s : b->s) ++s->steps;
-    if (!b->exec && k > 1 && (rc = capture_batch(b, k, &b->exec))) return rc;
-    if (!b->exec1 && (rc = capture_batch(b, 1, &b->exec1))) return rc;
-    if (k == 1) b->exec = b->exec1;
+  int64_t eager = k > 0 ? nsteps % k : nsteps;
+  if (k > 0 && eager == 0 && !b->launched) eager = k;
+  if (eager > 0) {
+    if ((rc = enqueue_steps(b, eager))) return rc;
+    b->launched = true;
   }
-  int64_t it = 0;
-  if (k > 0) {
-    for (; it + k <= nsteps; it += k) {
-      hipError_t e = hipGraphLaunch(b->exec, b->stream);
-      if (e != hipSuccess) return bfail(b, DGBGK_EDEVICE, "graph launch: %s", hipGetErrorString(e));
-    }
-    for (; it < nsteps; ++it) {
-      hipError_t e = hipGraphLaunch(b->exec1, b->stream);
-      if (e != hipSuccess) return bfail(b, DGBGK_EDEVICE, "graph launch: %s", hipGetErrorString(e));
-    }
-  } else if ((rc = enqueue_steps(b, nsteps - it))) {
-    return rc;
+  if (eager < nsteps && !b->exec && (rc = capture_batch(b, k, &b->exec))) return rc;
+  for (int64_t it = eager; it < nsteps; it += k) {
+    hipError_t e = hipGraphLaunch(b->exec, b->stream);
+    if (e != hipSuccess) return bfail(b, DGBGK_EDEVICE, "graph launch: %s", hipGetErrorString(e));
   }
   for (auto *s : b->s) {
     s->steps += nsteps;
