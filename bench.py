@@ -32,7 +32,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 ALG_BYTES_PER_DOF_STAGE = 32.0  # FP64 RK4, 3 registers: 24/40/40/24 B per stage -> 32 mean
-# what the FP64 kernels move (the accumulator written once per step): 16/32/24/32 -> 26 mean
+# what the FP64 kernels move (stage states instead of an accumulator): 16/24/24/40 -> 26 mean
 ALG_BYTES_PER_DOF_STAGE_KERNEL = 26.0
 # FP32 increment-form RK4: 12/20/20/16 B per stage -> 17 mean (what the
 # kernels move); the method's own FP32 figure (3 registers) is 16 B
@@ -40,8 +40,8 @@ ALG_BYTES_PER_DOF_STAGE_FP32 = 17.0
 ALG_BYTES_PER_DOF_STAGE_FP32_METHOD = 16.0
 # reference form: the FP32 increment form plus the FP32 L(f_r) read once per stage
 ALG_BYTES_PER_DOF_STAGE_REF = 21.0
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "stage_kernel_cavity64x64_p3_nc16_traffic.json")
-KERNEL_SRC = os.path.join(ROOT, "paper_2012_13487_amd", "csrc", "kernels.hip")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "rows_kernel_cavity64x64_p3_nc16_traffic.json")
+KERNEL_SRC = os.path.join(ROOT, "paper_2012_13487_amd", "csrc", "rows_kernel.hpp")
 
 
 def kernel_source_hash():
@@ -185,10 +185,10 @@ def batching(steps):
             g.init_equilibrium()
         tuned = {}
         if batched:
-            # the autotuner on every member (fused blocks of each admissible
-            # size and, in FP64, velocity tiles); the batch keeps the choice of
-            # members large enough to run their own kernels and gives the
-            # others the fused form
+            # the autotuner on every member (row kernels, fused blocks of each
+            # admissible size and, in FP64, velocity tiles); the batch keeps the
+            # choice of members large enough to run their own kernels and gives
+            # the others row kernels or the fused form
             for g in solvers:
                 g.autotune(3)
                 tuned[(g.p, g.Q)] = g.tiling()["elems_per_group"]
@@ -387,8 +387,7 @@ def couette_config1(repeats=5):
         g.set_graph(k)
         dt = g.stable_dt(spec.cfl)
         g.init_equilibrium()
-        # the autotuner's block size: alone, this 64-element problem runs fastest with
-        # one element per work-group (the automatic choice, 16, suits batches of it)
+        # (the autotuner finds the row kernels, the automatic choice, fastest here)
         g.autotune(200)  # (launches of a few us: fewer than ~100 let noise pick the block size)
         g.step(spec.steps, dt)  # warm-up (and the graph capture)
         times = []
@@ -599,7 +598,7 @@ def main():
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": traffic,
-            "kernel": "stage_kernel<3>",
+            "kernel": "rows_kernel<1, 3>",
             "avg_launch_us": stage_us,
             "alg_bytes_per_launch": ALG_BYTES_PER_DOF_STAGE * dof,
             "kernel_alg_bytes_per_launch": ALG_BYTES_PER_DOF_STAGE_KERNEL * dof,

@@ -2778,7 +2778,7 @@ int dgbgk_batch_step(dgbgk_batch *b, int64_t nsteps, const double *dt) {
     if ((rc = enqueue_steps(b, eager))) return rc;
     b->launched = true;
   }
-  if (eager < nsteps && !b->exec && (rc = capture_batch(b, k, &b->exec))) return rc;
+  if (k > 0 && nsteps >= k && !b->exec && (rc = capture_batch(b, k, &b->exec))) return rc;
   for (int64_t it = eager; it < nsteps; it += k) {
     hipError_t e = hipGraphLaunch(b->exec, b->stream);
     if (e != hipSuccess) return bfail(b, DGBGK_EDEVICE, "graph launch: %s", hipGetErrorString(e));
