@@ -294,6 +294,15 @@ int dgbgk_set_tiling(dgbgk_solver *s, int32_t mode, int32_t velocities_per_tile)
 int dgbgk_get_tiling(const dgbgk_solver *s, int32_t *fused, int32_t *elems_per_group,
                      int32_t *velocities_per_tile, size_t *lds_bytes);
 
+/* Which kernels the steps and residuals run now (any output may be NULL):
+ * *form 0: the block kernels, in the decomposition get_tiling reports; 1: the
+ * row kernels, an element's velocities over *wavefronts wavefronts of each of
+ * *velocity_tiles work-groups; 2: the row kernels, *elems_per_wavefront whole
+ * elements in a wavefront.  The outputs that a form does not name are 0 (form
+ * 0), else 1. */
+int dgbgk_get_step_form(const dgbgk_solver *s, int32_t *form, int32_t *wavefronts,
+                        int32_t *velocity_tiles, int32_t *elems_per_wavefront);
+
 /* Number of RK4 steps taken since the last init / set_state. */
 int dgbgk_steps_taken(const dgbgk_solver *s, int64_t *steps);
 

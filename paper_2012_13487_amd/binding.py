@@ -120,6 +120,8 @@ SIGNATURES = {
     "dgbgk_set_tiling": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32]),
     "dgbgk_get_tiling": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                    C.POINTER(C.c_int32), C.POINTER(C.c_size_t)]),
+    "dgbgk_get_step_form": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
+                                      C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "dgbgk_steps_taken": (C.c_int, [C.c_void_p, C.POINTER(C.c_int64)]),
     "dgbgk_set_block_elements": (C.c_int, [C.c_void_p, C.c_int32]),
     "dgbgk_autotune": (C.c_int, [C.c_void_p, C.c_int32, _dp]),
@@ -347,6 +349,13 @@ class Solver:
         return {"fused": bool(fused.value), "persistent": fused.value == 2,
                 "elems_per_group": e.value, "velocities_per_tile": qt.value,
                 "lds_bytes": lds.value}
+
+    def step_form(self):
+        """Which kernels the steps run: form 0 block kernels (see tiling()), 1 row kernels with an
+        element over several wavefronts, 2 row kernels with whole elements in a wavefront."""
+        v = [C.c_int32() for _ in range(4)]
+        self._call("dgbgk_get_step_form", *[C.byref(x) for x in v])
+        return dict(zip(("form", "wavefronts", "velocity_tiles", "elems_per_wavefront"), [x.value for x in v]))
 
     # -- device work
     def init_moments(self, rho, ux, uy):

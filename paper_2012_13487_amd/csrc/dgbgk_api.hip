@@ -1513,6 +1513,17 @@ int dgbgk_get_tiling(const dgbgk_solver *s, int32_t *fused, int32_t *elems_per_g
   return DGBGK_OK;
 }
 
+int dgbgk_get_step_form(const dgbgk_solver *s, int32_t *form, int32_t *wavefronts,
+                        int32_t *velocity_tiles, int32_t *elems_per_wavefront) {
+  if (!s) return fail(nullptr, DGBGK_EINVAL, "solver is NULL");
+  const RowPlan &r = s->rows;
+  if (form) *form = r.kind;
+  if (wavefronts) *wavefronts = r.kind ? r.nw : 0;
+  if (velocity_tiles) *velocity_tiles = r.kind ? r.nt : 0;
+  if (elems_per_wavefront) *elems_per_wavefront = r.kind ? r.ew : 0;
+  return DGBGK_OK;
+}
+
 }  // extern "C"
 
 // ---- block size, autotuner -----------------------------------------------------
