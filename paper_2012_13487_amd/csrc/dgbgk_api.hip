@@ -139,6 +139,7 @@ struct dgbgk_solver {
   // between steps) and whether slot 0 holds those of the current f_n
   double *d_part[2] = {nullptr, nullptr};
   bool part_valid = false;
+  bool replayed = false;  // calls are in a graph of the caller's, whose replays change f_n unseen
   // reference form: f = f_ref + g (FP64 reference, FP32 correction in the registers)
   double *d_fref = nullptr, *d_mref = nullptr;
   float *g_rref = nullptr;
@@ -647,6 +648,19 @@ int run_stage(dgbgk_solver *s, int stage, const void *fs_, void *out_, double dt
   return DGBGK_OK;
 }
 
+// Calls recorded into a caller's graph run again, on whatever state is there
+// then, without the library seeing it: such a call reduces the moments of f_n
+// itself, and from then on every later call of the solver does (one pass over
+// the state).  At the start of each call that enqueues work on st and returns.
+void note_capture(dgbgk_solver *s, hipStream_t st) {
+  if (!s->replayed && st) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) (void)hipGetLastError();
+    s->replayed = c != hipStreamCaptureStatusNone;
+  }
+  if (s->replayed) s->part_valid = false;
+}
+
 // Reference form: r = L(f_ref) by the FP64 stage kernel (into the FP64
 // transfer buffer, then rounded to FP32), and the node moments of f_ref.
 int ref_refresh(dgbgk_solver *s) {
@@ -992,6 +1006,7 @@ int dgbgk_init_equilibrium(dgbgk_solver *s, double rho0, double ux0, double uy0)
     return fail(s, DGBGK_EINVAL, "rho0 must be > 0 and u0 finite");
   int rc = ensure_device(s);
   if (rc) return rc;
+  note_capture(s, s->stream);
   hipError_t e =
       is_ref(s->prec)
           ? launch_init_equilibrium(s->d_fref, s->d_vel, (int)s->K, s->Np, s->Q, rho0, ux0, uy0,
@@ -1296,11 +1311,13 @@ int dgbgk_step(dgbgk_solver *s, int64_t nsteps, double dt) {
   if (!s->have_state) return fail(s, DGBGK_ESTATE, "no state: call init or set_state first");
   int rc = ensure_device(s);
   if (rc) return rc;
+  note_capture(s, s->stream);
   int64_t it = 0;
   if (s->graph_steps > 0 && nsteps >= s->graph_steps) {
+    // (the captured first stage reads the partials of f_n)
+    if (s->gexec && s->graph_partials && (rc = ensure_partials(s))) return rc;
     const int cfg[6] = {s->fused, s->E, s->Qt, s->persistent, s->prec, s->rows.kind};
-    if (!s->gexec || s->graph_dt != dt || std::memcmp(cfg, s->graph_cfg, sizeof cfg) != 0 ||
-        (s->graph_partials && !s->part_valid)) {
+    if (!s->gexec || s->graph_dt != dt || std::memcmp(cfg, s->graph_cfg, sizeof cfg) != 0) {
       // one eager step first: it sets the kernels' LDS attributes outside the capture
       if ((rc = enqueue_rk4_step(s, dt))) return rc;
       ++s->steps;
@@ -1385,6 +1402,7 @@ int dgbgk_wall_density(dgbgk_solver *s, const double *f, double *out, size_t cou
 }
 
 static int residual_enqueue(dgbgk_solver *s) {
+  note_capture(s, s->stream);
   int rc = ensure_partials(s);
   if (rc) return rc;
   const double *pin;
@@ -1457,6 +1475,7 @@ int dgbgk_fold(dgbgk_solver *s) {
   if (!s) return fail(nullptr, DGBGK_EINVAL, "solver is NULL");
   if (!is_ref(s->prec)) return fail(s, DGBGK_ENOTSUP, "only the reference form has a correction to fold");
   if (!s->have_state) return fail(s, DGBGK_ESTATE, "no state: call init or set_state first");
+  note_capture(s, s->stream);
   hipError_t e = launch_ref_fold(s->d_fref, s->g_fn, (size_t)s->K * s->Np * s->Q, s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "fold kernel");
   s->part_valid = false;  // the correction is zero now
@@ -2416,6 +2435,7 @@ int batch_partials(dgbgk_batch *b) {
     dgbgk_solver *s = b->s[i];
     hipStream_t own = s->stream;
     s->stream = b->stream;
+    note_capture(s, s->stream);
     const int rc = ensure_partials(s);
     s->stream = own;
     if (rc) return bfail(b, rc, "member %zu: %s", i, s->err.c_str());
