@@ -176,6 +176,12 @@ struct dgbgk_solver {
 
 namespace {
 
+// HIP keeps the last error of a thread until it is read; the launchers read it
+// after a launch, so one that a call has reported must not be there any more.
+void clear_reported(int code) {
+  if (code == DGBGK_EDEVICE || code == DGBGK_ENOMEM) (void)hipGetLastError();
+}
+
 int fail(dgbgk_solver *s, int code, const char *fmt, ...) {
   char buf[512];
   va_list ap;
@@ -184,6 +190,7 @@ int fail(dgbgk_solver *s, int code, const char *fmt, ...) {
   va_end(ap);
   if (s) s->err = buf;
   else g_create_error = buf;
+  clear_reported(code);
   return code;
 }
 
@@ -2365,6 +2372,7 @@ int bfail(dgbgk_batch *b, int code, const char *fmt, ...) {
   va_end(ap);
   if (b) b->err = buf;
   else g_create_error = buf;
+  clear_reported(code);
   return code;
 }
 

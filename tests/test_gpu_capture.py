@@ -135,3 +135,38 @@ def test_replayed_batch_steps_follow_the_states_that_are_there(prec):
     b.close()
     for g, _ in pairs:
         g.set_stream(None)
+
+
+def _failed_capture():
+    """A batch of one solver whose call of three steps took one and could not
+    capture the graph of the rest: the stream is being captured already."""
+    import torch
+    side = torch.cuda.Stream()
+    g = binding.Solver.from_spec(_spec(2, 16, 5, 4, "cavity"), stream=side.cuda_stream)
+    g.set_state(_state(g, 3))
+    b = binding.Batch([g], stream=side.cuda_stream)
+    dt = [g.stable_dt(0.2)]
+    b.step(1, dt)
+    b.set_graph(2)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        with pytest.raises(binding.DgbgkError) as e:
+            b.step(3, dt)
+    assert e.value.code == binding.EDEVICE
+    torch.cuda.synchronize()
+    return g, b, dt
+
+
+def test_an_error_is_reported_once():
+    """The calls after a reported HIP error work: its last-error slot is empty."""
+    print("[gpu] calls after a failed capture", flush=True)
+    g, b, dt = _failed_capture()
+    h = binding.Solver.from_spec(_spec(2, 16, 5, 4, "cavity"))
+    for s in (g, h):
+        s.set_state(_state(g, 4))
+    b.step(4, dt)
+    h.step(4, dt[0])
+    assert np.array_equal(g.get_state(), h.get_state())
+    b.close()
+    g.set_stream(None)
