@@ -2816,16 +2816,15 @@ int dgbgk_batch_step(dgbgk_batch *b, int64_t nsteps, const double *dt) {
   if (eager > 0) {
     if ((rc = enqueue_steps(b, eager))) return rc;
     b->launched = true;
+    for (auto *s : b->s) s->steps += eager;
   }
   if (k > 0 && nsteps >= k && !b->exec && (rc = capture_batch(b, k, &b->exec))) return rc;
   for (int64_t it = eager; it < nsteps; it += k) {
     hipError_t e = hipGraphLaunch(b->exec, b->stream);
     if (e != hipSuccess) return bfail(b, DGBGK_EDEVICE, "graph launch: %s", hipGetErrorString(e));
+    for (auto *s : b->s) s->steps += k;
   }
-  for (auto *s : b->s) {
-    s->steps += nsteps;
-    s->part_valid = uses_partials(s);  // each step ends with the partials of f_n in P0
-  }
+  for (auto *s : b->s) s->part_valid = uses_partials(s);  // each step ends with the partials of f_n in P0
   return DGBGK_OK;
 }
 

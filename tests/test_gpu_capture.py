@@ -170,3 +170,13 @@ def test_an_error_is_reported_once():
     assert np.array_equal(g.get_state(), h.get_state())
     b.close()
     g.set_stream(None)
+
+
+def test_a_batch_counts_the_steps_it_enqueued_before_a_failure():
+    print("[gpu] batch: steps counted before a failed capture", flush=True)
+    g, b, dt = _failed_capture()
+    assert g.steps_taken() == 2  # (one before, one in the failed call)
+    b.step(5, dt)                # (an eager one and two replays)
+    assert g.steps_taken() == 7
+    b.close()
+    g.set_stream(None)
