@@ -6,6 +6,7 @@ namespace dgbgk {
 RowPlan row_plan(int p, int64_t K, int Q, int size, bool ref) {
   RowPlan r;
   if (p < 1 || p > kRowMaxP || Q < kRowMinQ || K < 1) return r;
+  const int64_t most_waves = (((int64_t)1 << 32) - 1) / 64;  // a launch holds fewer than 2^32 threads along x
   const int n1 = p + 1, np = n1 * n1, pr = row_period(np, size);
   const int fit = row_elements_max(np, size, Q);
   if (fit >= 1) {
@@ -14,6 +15,7 @@ RowPlan row_plan(int p, int64_t K, int Q, int size, bool ref) {
     r.kind = 2;
     r.ew = fit < 4 ? fit : 4;
     while (r.ew > 1 && (K + r.ew - 1) / r.ew < 512) r.ew = (r.ew + 1) / 2;
+    if ((K + r.ew - 1) / r.ew > most_waves) return RowPlan{};
     r.nw = 1;
     r.nblk = (int)((K + r.ew - 1) / r.ew);
     r.lds = (size_t)row_elements_bytes(n1, size, ref, r.ew);
@@ -33,7 +35,7 @@ RowPlan row_plan(int p, int64_t K, int Q, int size, bool ref) {
       r.nt = nt;
     }
   }
-  if (best == 1 << 30) return r;
+  if (best == 1 << 30 || K * r.nw > most_waves) return RowPlan{};
   r.kind = 1;
   r.ew = 1;
   r.nblk = (int)K;

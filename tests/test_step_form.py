@@ -42,3 +42,14 @@ def test_choices_that_run_the_block_kernels():
                        (workloads.cavity(n=4, p=3, m=40), binding.FP64),
                        (workloads.cavity(n=4, p=2, m=8), binding.FP32_BF16MMA)):
         assert binding.Solver.from_spec(spec, precision=prec).step_form() == BLOCKS
+
+
+def test_meshes_beyond_one_launch_of_the_row_kernels_run_the_block_kernels():
+    """A launch holds fewer than 2^32 threads along x: 256 per element of 196
+    velocities, 64 per element of 36, 128 per element of 81."""
+    box = lambda nx, ny, n: workloads.periodic_box(nx=nx, ny=ny, p=1, velset=("gh", n))  # noqa: E731
+    assert _form(box(4095, 4096, 14)) == (1, 4, 1, 1) and _form(box(4096, 4096, 14))[0] == 0
+    assert _form(box(8191, 8192, 6)) == (2, 1, 1, 1) and _form(box(8192, 8192, 6))[0] == 0
+    assert _form(box(4096, 8191, 9)) == (1, 2, 1, 1) and _form(box(4096, 8192, 9))[0] == 0
+    t = binding.Solver.from_spec(box(4096, 8192, 9)).tiling()  # (several elements per work-group of 256)
+    assert t["fused"] and t["elems_per_group"] >= 2
