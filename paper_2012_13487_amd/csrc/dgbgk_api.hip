@@ -53,12 +53,21 @@ bool is_bf(int precision) { return precision == DGBGK_FP32_BF16MMA || precision 
 bool is_ref(int precision) { return precision == DGBGK_FP32_REF || precision == DGBGK_FP32_BF16MMA_REF; }
 bool valid_precision(int precision) { return precision == DGBGK_FP64 || is_fp32(precision); }
 
-// Velocity tiles whose moment partials a state of this precision keeps.
-int part_tiles(int precision, int Nfp, int Q) {
+// Velocity tiles whose moment partials a state of this precision has a region for.
+int part_tiles(int precision, int Nfp) {
   if (precision == DGBGK_FP64) return kMaxPartialTiles;
-  const RowPlan r = is_bf(precision) ? RowPlan{} : row_plan(Nfp - 1, 1, Q, 4, is_ref(precision));
-  if (r.kind == 1) return r.nt;
   return (Nfp == 2 || Nfp == 4) ? 1 : 0;  // the orders whose one-element blocks hand moments over (1 and 3)
+}
+
+// FP32 row plans of more tiles than that keep their partials in the FP64
+// transfer buffer (Q doubles per node; two slots of 7 per tile, at most
+// 2 + Q / 128 tiles and at least 62 velocities), so that a solver needs no more
+// memory for them.  A call that moves a state through the buffer leaves them
+// stale (transfer_buffer).
+bool part_in_transfer(int precision, int p, int Q) {
+  if (precision == DGBGK_FP64 || is_bf(precision)) return false;
+  const RowPlan r = row_plan(p, 1, Q, 4, is_ref(precision));
+  return r.kind == 1 && r.nt > part_tiles(precision, p + 1);
 }
 
 // State registers (FP64, or the FP32 deviation), an FP64 transfer buffer for
@@ -86,10 +95,10 @@ Layout make_layout(int64_t K, int Np, int Nfp, int Q, int precision) {
   L.rref = off; off += ref ? round_up(ndof * sizeof(float)) : 0;
   L.mref = off; off += ref ? round_up((size_t)3 * K * Np * sizeof(double)) : 0;
   // moment partials of two states (the state a stage reads, the one it
-  // writes): FP64 up to kMaxPartialTiles velocity tiles each; FP32 storage those
-  // of its row plan, or one (one-element blocks of orders 1 and 3)
+  // writes): FP64 up to kMaxPartialTiles velocity tiles each; FP32 storage one
+  // (one-element blocks of orders 1 and 3)
   L.part = off;
-  off += 2 * round_up((size_t)part_tiles(precision, Nfp, Q) * K * 7 * Np * sizeof(double));
+  off += 2 * round_up((size_t)part_tiles(precision, Nfp) * K * 7 * Np * sizeof(double));
   L.total = off;
   return L;
 }
@@ -139,6 +148,7 @@ struct dgbgk_solver {
   // between steps) and whether slot 0 holds those of the current f_n
   double *d_part[2] = {nullptr, nullptr};
   bool part_valid = false;
+  bool part_in_xfer = false;  // they lie in the transfer buffer
   bool replayed = false;  // calls are in a graph of the caller's, whose replays change f_n unseen
   // reference form: f = f_ref + g (FP64 reference, FP32 correction in the registers)
   double *d_fref = nullptr, *d_mref = nullptr;
@@ -368,9 +378,12 @@ int ensure_device(dgbgk_solver *s) {
   s->d_mom = (double *)(b + s->lay.mom);
   s->d_rhow = (double *)(b + s->lay.rhow);
   s->d_u64 = (unsigned long long *)(b + s->lay.u64);
-  if (const int pt = part_tiles(s->prec, s->Nfp, s->Q)) {
-    s->d_part[0] = (double *)(b + s->lay.part);
-    s->d_part[1] = (double *)(b + s->lay.part + round_up((size_t)pt * s->K * 7 * s->Np * sizeof(double)));
+  s->part_in_xfer = part_in_transfer(s->prec, s->p, s->Q);
+  const int pt = s->part_in_xfer ? row_plan(s->p, s->K, s->Q, 4, is_ref(s->prec)).nt : part_tiles(s->prec, s->Nfp);
+  if (pt) {
+    char *at = b + (s->part_in_xfer ? s->lay.xfer : s->lay.part);
+    s->d_part[0] = (double *)at;
+    s->d_part[1] = (double *)(at + round_up((size_t)pt * s->K * 7 * s->Np * sizeof(double)));
   }
   if (is_ref(s->prec)) {
     s->d_fref = (double *)(b + s->lay.fref);
@@ -655,6 +668,12 @@ int run_stage(dgbgk_solver *s, int stage, const void *fs_, void *out_, double dt
   return DGBGK_OK;
 }
 
+// The transfer buffer of the FP32 precisions, for a call that writes it.
+double *transfer_buffer(dgbgk_solver *s) {
+  if (s->part_in_xfer) s->part_valid = false;
+  return s->d_xfer;
+}
+
 // Calls recorded into a caller's graph run again, on whatever state is there
 // then, without the library seeing it: such a call reduces the moments of f_n
 // itself, and from then on every later call of the solver does (one pass over
@@ -690,7 +709,7 @@ int ref_refresh(dgbgk_solver *s) {
   a.fs = s->d_fref;
   a.fn = s->d_fref;
   a.acc = nullptr;
-  a.out = s->d_xfer;
+  a.out = transfer_buffer(s);
   a.stage = 0;
   e = launch_stage(s->p, a, c.lds, c.ntiles, s->stream);
   if (e == hipSuccess) e = launch_f64_to_f32(s->d_xfer, s->g_rref, n, s->stream);
@@ -1080,7 +1099,7 @@ int dgbgk_set_state(dgbgk_solver *s, const double *f, size_t count) {
   // host order f[q][k][n] into a staging buffer, then element-major into f_n
   hipError_t e;
   if (is_ref(s->prec)) {
-    e = hipMemcpyAsync(s->d_xfer, f, need * sizeof(double), hipMemcpyHostToDevice, s->stream);
+    e = hipMemcpyAsync(transfer_buffer(s), f, need * sizeof(double), hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess) e = launch_transpose(s->d_xfer, s->d_fref, (int)s->K, s->Np, s->Q, 1, s->stream);
     if (e == hipSuccess) {
       // the transfer buffer is reused by the reference's right-hand side
@@ -1088,7 +1107,7 @@ int dgbgk_set_state(dgbgk_solver *s, const double *f, size_t count) {
       if (e == hipSuccess && (rc = ref_reset(s))) return rc;
     }
   } else if (is_fp32(s->prec)) {
-    e = hipMemcpyAsync(s->d_xfer, f, need * sizeof(double), hipMemcpyHostToDevice, s->stream);
+    e = hipMemcpyAsync(transfer_buffer(s), f, need * sizeof(double), hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess)
       e = launch_to_dev32(s->d_xfer, s->g_fn, s->d_vel, (int)s->K, s->Np, s->Q, s->rho_ref, s->stream);
   } else {
@@ -1108,7 +1127,7 @@ int dgbgk_get_state(dgbgk_solver *s, double *f, size_t count) {
   const size_t need = (size_t)s->K * s->Np * s->Q;
   if (!f || count != need) return fail(s, DGBGK_EINVAL, "state needs %zu doubles", need);
   if (!s->have_state) return fail(s, DGBGK_ESTATE, "no state: call init or set_state first");
-  double *stage = is_fp32(s->prec) ? s->d_xfer : s->d_b;
+  double *stage = is_fp32(s->prec) ? transfer_buffer(s) : s->d_b;
   hipError_t e = is_ref(s->prec)
                      ? launch_from_ref(s->d_fref, s->g_fn, stage, (int)s->K, s->Np, s->Q, s->stream)
                  : is_fp32(s->prec)
@@ -1355,7 +1374,7 @@ int dgbgk_rhs(dgbgk_solver *s, const double *f, double *k, size_t count) {
     if (is_ref(s->prec) && !s->have_state)
       return fail(s, DGBGK_ESTATE, "the reference form evaluates L(f) as a correction to its "
                                    "reference: call init or set_state first");
-    e = hipMemcpyAsync(s->d_xfer, f, need * sizeof(double), hipMemcpyHostToDevice, s->stream);
+    e = hipMemcpyAsync(transfer_buffer(s), f, need * sizeof(double), hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess)
       e = is_ref(s->prec)
               ? launch_to_ref(s->d_xfer, s->d_fref, s->g_a, (int)s->K, s->Np, s->Q, s->stream)
@@ -1390,7 +1409,7 @@ int dgbgk_wall_density(dgbgk_solver *s, const double *f, double *out, size_t cou
   int rc = ensure_device(s);
   if (rc) return rc;
   const bool f32 = is_fp32(s->prec);
-  hipError_t e = hipMemcpyAsync(f32 ? s->d_xfer : s->d_b, f, need * sizeof(double),
+  hipError_t e = hipMemcpyAsync(f32 ? transfer_buffer(s) : s->d_b, f, need * sizeof(double),
                                 hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess)
     e = f32 ? launch_to_dev32(s->d_xfer, s->g_a, s->d_vel, (int)s->K, s->Np, s->Q, s->rho_ref,
