@@ -1141,8 +1141,10 @@ template <int KIND>
 constexpr int row_threads() { return KIND == kKindWave ? 64 : 256; }
 
 // Wavefronts per SIMD asked of the compiler: what fits without spilling a
-// register (a value stored to scratch where some lanes are switched off is not
-// stored for them: a request that spilled gave wrong rates).
+// vector register; the build refuses scratch in these kernels.  A request that
+// spilled once gave wrong rates.  Why is not known: in 69 instantiations compiled
+// to spill, and not run, every reload reads what the lanes that are on there
+// had stored.
 template <int KIND, int P, typename T, int MODE>
 constexpr int row_waves() {
   if (KIND == kKindSums) return 1;
