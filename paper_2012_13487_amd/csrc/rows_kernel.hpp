@@ -1150,9 +1150,7 @@ constexpr int row_waves() {
   if (KIND == kKindSums) return 1;
   if (MODE == kRateSums && P == 4) return sizeof(T) == 8 && KIND == kKindWave ? 2 : 3;
   if (KIND == kKindWave) return sizeof(T) == 8 ? (P <= 2 ? 4 : P == 3 ? 3 : 2) : 4;
-  // (the last FP64 stage streams five arrays: with more wavefronts than three
-  // its neighbours' faces fall out of L2, p = 3: 117 us with three, 130 with four)
-  if (sizeof(T) == 8) return P == 1 ? 6 : P == 2 ? 5 : P == 3 && MODE != 4 ? 4 : 3;
+  if (sizeof(T) == 8) return P == 1 ? 6 : P == 2 ? 5 : P == 3 ? 4 : 3;
   return P == 1 ? 6 : P == 2 ? 5 : 4;
 }
 
