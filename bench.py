@@ -118,6 +118,13 @@ def time_steps(solver, steps, dt):
     return a.elapsed_time(b)
 
 
+def kernels_of(g):
+    """Which kernels the solver's steps run: the row kernels' plan, or the block
+    kernels' decomposition."""
+    form = g.step_form()
+    return {"tiling": g.tiling()} if form["form"] == 0 else {"rows": form}
+
+
 def precision_path(steps_small, steps_big):
     """DOF-updates/s of the FP32-storage path next to FP64, on the benchmark
     workload and on the precision workload (all inputs resident in HBM)."""
@@ -144,7 +151,7 @@ def precision_path(steps_small, steps_big):
             entry[prec] = {"value": g.ndof * 4 * steps / (ms / 1000.0), "unit": "DOF-updates/s",
                            "avg_launch_us": stage_us, "alg_bytes_per_dof_stage": bpd,
                            "achieved_GBs": ach, "frac": ach / HBM_PEAK_GBS, "steps": steps,
-                           "tiling": g.tiling()}
+                           **kernels_of(g)}
             if prec in ("fp32", "fp32_bf16mma"):
                 # the method's 3-register FP32 figure, beside the increment form's
                 m = ALG_BYTES_PER_DOF_STAGE_FP32_METHOD * g.ndof / (stage_us * 1e-6) / 1e9
@@ -191,7 +198,7 @@ def batching(steps):
             # the others row kernels or the fused form
             for g in solvers:
                 g.autotune(3)
-                tuned[(g.p, g.Q)] = g.tiling()["elems_per_group"]
+                tuned[(g.p, g.Q)] = kernels_of(g)
         dts = np.array([g.stable_dt(sp.cfl) for g, sp in zip(solvers, specs)])
         dof = sum(g.ndof for g in solvers)
         if batched:
@@ -397,7 +404,7 @@ def couette_config1(repeats=5):
         ms = sorted(times)[len(times) // 2]
         out[name] = {"value": g.ndof * 4 * spec.steps / (ms / 1000.0), "unit": "DOF-updates/s",
                      "ms_per_solve": ms, "us_per_stage": 1000.0 * ms / (4 * spec.steps),
-                     "steps_per_graph": k, "tiling": g.tiling()}
+                     "steps_per_graph": k, **kernels_of(g)}
         out["dof"] = g.ndof
         g.close()
     out["graph_over_eager"] = out["graph"]["value"] / out["eager"]["value"]

@@ -209,10 +209,17 @@ int dgbgk_get_state(dgbgk_solver *s, double *f, size_t count);
 /* Device address of the current state, element-major f[k][q][n] (FP64,
  * Q*K*Np doubles; for the FP32 precisions the FP32 deviation g[k][q][n] =
  * f - w_q; for the reference forms the FP32 correction g = f - f_r), valid
- * until the next dgbgk_step(); for zero-copy views. */
+ * until the next dgbgk_step(); for zero-copy views that read it.  A state is
+ * changed with dgbgk_set_state or the init calls: the steps take the node
+ * moments of f from the stage that wrote it (see dgbgk_set_tiling), so a value
+ * written through the address would not be in them. */
 int dgbgk_state_device_ptr(dgbgk_solver *s, void **ptr);
 
 /* Advance nsteps classical RK4 steps of size dt (enqueued; returns at once).
+ * Like dgbgk_residual_async, dgbgk_fold and dgbgk_batch_step it may be recorded
+ * into a graph of the caller's (its stream being captured) once the solver has
+ * stepped; from then on the solver reduces the moments of its state at the start
+ * of each call, since a replay changes the state unseen.
  * Each step runs the four stages of the right-hand side
  *   L(f)_q = -e_q . grad f_q  (volume)  + lifted upwind face flux  (surface)
  *            - (f_q - f_q^eq(rho, u)) / tau  (collision)

@@ -165,19 +165,20 @@ hipError_t launch_rate_max(const double *part, int K, int Np, int nt, double sca
 hipError_t launch_rows_sums(int p, const RowArgs<double> &a, size_t lds, hipStream_t st);
 hipError_t launch_rows_sums32(int p, const RowArgs<float> &a, size_t lds, hipStream_t st);
 
-// Batched stages: one work-group of 256 threads per item (problem, work-group;
-// row_items of them per problem), descriptors as in launch_batch_stage, problems
-// of order p; lds: the largest row_item_lds.
-// A plan's work-groups of 256 threads: two elements each where two wavefronts
-// take one, else one; four wavefronts' runs of elements.
+// A plan's work-groups of 256 threads in a batch: two elements each where two
+// wavefronts take one, else one; four wavefronts' runs of elements.
 inline int row_items(const RowPlan &r) {
   const int per = r.kind == 2 ? 4 : r.nw == 2 ? 2 : 1;
   return (r.nblk * r.nt + per - 1) / per;
 }
 inline size_t row_item_lds(const RowPlan &r) { return (r.kind == 2 ? 4 : r.nw == 2 ? 2 : 1) * r.lds; }
-hipError_t launch_batch_rows(int p, int stage, const RowArgs<double> *descs, const int2 *items, int nitems, size_t lds,
-                             hipStream_t st);
-hipError_t launch_batch_rows32(int p, int ref, int stage, const RowArgs<float> *descs, const int2 *items, int nitems,
-                               size_t lds, hipStream_t st);
+
+// Batched stages: one work-group of 256 threads per item (problem, work-group;
+// row_items of them per problem), descriptors as in launch_batch_stage, problems
+// of order p; lds: the largest row_item_lds.
+hipError_t launch_batch_rows(int p, int stage, const RowArgs<double> *descs, const int2 *items, int nitems,
+                             size_t lds, hipStream_t st);
+hipError_t launch_batch_rows32(int p, int ref, int stage, const RowArgs<float> *descs, const int2 *items,
+                               int nitems, size_t lds, hipStream_t st);
 
 }  // namespace dgbgk

@@ -13,9 +13,10 @@
 //
 // The node moments the collision needs are sums over all velocities:
 //  * handed over (more velocities than a wavefront has rows): one element, and
-//    up to 256 of its velocities, per work-group; the update pass also sums 1, e_x, e_y (and, at walls, the
-//    outgoing normal speeds) times its outputs per node, and the next stage
-//    reads the sums (7 Np doubles per element) before its rows;
+//    up to 256 of its velocities, per work-group; the update pass also sums 1,
+//    e_x, e_y (and, at walls, the outgoing normal speeds) times its outputs per
+//    node, and the next stage reads the sums (7 Np doubles per element) before
+//    its rows;
 //  * in the wavefront (an element's rows fit a wavefront): the wavefront owns
 //    whole elements and sums over the velocities from its tile.
 //
@@ -551,9 +552,9 @@ struct Operands {
 // results; off: offset of the tile's first row in the states), and with SUM the
 // column sums of its outputs, with keep the outputs back into the tile.  ev:
 // e_x, e_y of the tile's rows.  (Its operands loaded before the rows are
-// evaluated, where registers allow it, measured 2 to 15% slower.)  WHOLE: 64 rows of this element; else rows of another one (the
-// lead, or what the last access holds beyond this element) are neither stored
-// nor summed.
+// evaluated, where registers allow it, measured 2 to 15% slower.)  WHOLE: 64
+// rows of this element; else rows of another one (the lead, or what the last
+// access holds beyond this element) are neither stored nor summed.
 template <int P, typename T, int MODE, bool REF, bool NT, bool SUM, bool WHOLE, typename A>
 __device__ __forceinline__ void rows_update_pass(const A &a, T *tile, const d2 *ev, ptrdiff_t off, int lo, int hi,
                                                  int lane, bool keep, ColumnSums<T> &cs) {
@@ -997,7 +998,9 @@ __device__ __forceinline__ void rows_wave(const A &a, int w, char *lds) {
   const int lead = (int)(row0 % Sh::PR);
   const ptrdiff_t base = (ptrdiff_t)(row0 - lead) * NP;
   const int hi = lead + Eb * Q;  // at most 64
-  const int r = max(min(lane, hi - 1) - lead, 0), er = (r >= Q) + (r >= 2 * Q) + (r >= 3 * Q), q = r - er * Q, kr = k0 + er;  // this lane's row
+  // this lane's row
+  const int r = max(min(lane, hi - 1) - lead, 0), er = (r >= Q) + (r >= 2 * Q) + (r >= 3 * Q), q = r - er * Q,
+            kr = k0 + er;
   const int ey0 = quotient(k0, a.dnx), ex0 = k0 - ey0 * a.nx;
   int exr, eyr;
   step_place(ex0, ey0, er, a, exr, eyr);
@@ -1119,8 +1122,9 @@ __device__ __forceinline__ void rows_wave(const A &a, int w, char *lds) {
 // ---- kernels ---------------------------------------------------------------------
 
 // The b-th work-group's place: the 8 XCDs take work-groups round-robin, so
-// each gets a contiguous run, swept in strips 16 elements wide, so that the work-groups resident on one XCD cover a compact
-// patch and find their neighbours' faces in its L2.
+// each gets a contiguous run, swept in strips 16 elements wide, so that the
+// work-groups resident on one XCD cover a compact patch and find their
+// neighbours' faces in its L2.
 __device__ __forceinline__ int xcd_run(int b, int n) {
   const int per = n >> 3, rem = n & 7, x = b & 7;
   return x * per + (x < rem ? x : rem) + (b >> 3);
@@ -1170,7 +1174,8 @@ __device__ __forceinline__ void rows_body(const A &a, int b, int vt, char *lds) 
 }
 
 template <int KIND, int P, typename T, int MODE, bool REF, typename A>
-__global__ __launch_bounds__(row_threads<KIND>()) __attribute__((amdgpu_waves_per_eu(row_waves<KIND, P, T, MODE>(), row_waves_most<KIND, P, T, MODE>())))
+__global__ __launch_bounds__(row_threads<KIND>())
+__attribute__((amdgpu_waves_per_eu(row_waves<KIND, P, T, MODE>(), row_waves_most<KIND, P, T, MODE>())))
 void rows_kernel(const A a) {
   extern __shared__ char row_lds[];
   const int b = strip_place(xcd_run(blockIdx.x, a.nblk), a);
@@ -1203,7 +1208,8 @@ __device__ __forceinline__ void rows_item(const A &a, int at, char *lds) {
 // the XCDs take them; the arguments come from a descriptor table in the constant
 // address space (scalar loads).
 template <int P, typename T, int MODE, bool REF, typename A>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(row_waves<kKindWave, P, T, MODE>(), row_waves_most<kKindWave, P, T, MODE>())))
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(row_waves<kKindWave, P, T, MODE>(), row_waves_most<kKindWave, P, T, MODE>())))
 void batch_rows_kernel(const A *descs, const int2 *items, int nitems) {
   extern __shared__ char row_lds[];
   const int2 it = items[blockIdx.x];
@@ -1226,7 +1232,8 @@ hipError_t launch_one(const A &a, size_t lds, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   const int threads = kind == kKindElement ? 64 * a.nw : 64;
-  hipLaunchKernelGGL((rows_kernel<KIND, P, T, MODE, REF, A>), dim3((unsigned)a.nblk, kind == kKindElement ? (unsigned)a.nt : 1u), dim3(threads), lds, st, a);
+  const dim3 grid((unsigned)a.nblk, kind == kKindElement ? (unsigned)a.nt : 1u);
+  hipLaunchKernelGGL((rows_kernel<KIND, P, T, MODE, REF, A>), grid, dim3(threads), lds, st, a);
   return hipGetLastError();
 }
 
