@@ -2261,6 +2261,16 @@ int implicit_steps(dgbgk_solver *s, int32_t scheme, int64_t nsteps, double dt,
   im.host_coef.assign(kMaxBasis, 0.0);
   im.twice.assign(im.m, 0);
 
+  // A call that fails may have work enqueued ahead of what the host has read; it
+  // ends before the call returns, as the workspace may be another solver's next.
+  struct Drain {
+    hipStream_t st;
+    bool done = false;
+    ~Drain() {
+      if (!done) (void)hipStreamSynchronize(st);
+    }
+  } drain{s->stream};
+
   const double rms = std::sqrt((double)n);  // 2-norm -> RMS
   int newton_total = 0, krylov_total = 0;
   double worst = 0.0;
@@ -2314,6 +2324,7 @@ int implicit_steps(dgbgk_solver *s, int32_t scheme, int64_t nsteps, double dt,
     ++s->steps;
   }
   hipError_t e = hipStreamSynchronize(s->stream);
+  drain.done = true;
   if (e != hipSuccess) return hip_fail(s, e, "implicit step");
   if (report) {
     report->newton_iterations = newton_total;
