@@ -294,7 +294,8 @@ int dgbgk_synchronize(dgbgk_solver *s);
  * (init, set_state, an implicit step, a fold), and in every stage of the block
  * kernels with more than four tiles.  get_tiling reports *fused = 0 (velocity
  * tiles), 1 (fused, one work-group per block) or 2 (fused, persistent), and the
- * LDS bytes per work-group.  The fused forms give bit-identical results, except
+ * LDS bytes per work-group; dgbgk_get_step_form which kernels the steps run.
+ * The fused forms give bit-identical results, except
  * one element per work-group at orders 1 and 3 (moments handed over: another
  * summation order); the tiled form and the row kernels agree to rounding. */
 int dgbgk_set_tiling(dgbgk_solver *s, int32_t mode, int32_t velocities_per_tile);
@@ -315,15 +316,17 @@ int dgbgk_steps_taken(const dgbgk_solver *s, int64_t *steps);
 
 /* Elements per work-group of the fused forms of the block kernels (0 =
  * automatic: the steps run the row kernels where they apply, see
- * dgbgk_set_tiling).  The value must divide into a tile that fits in LDS; DGBGK_EINVAL otherwise (the previous
- * choice is kept).  Changing it changes the summation order of the node
- * moments, so results agree with other choices to rounding, not bit for bit. */
+ * dgbgk_set_tiling).  The value must divide into a tile that fits in LDS;
+ * DGBGK_EINVAL otherwise (the previous choice is kept).  Changing it changes the
+ * summation order of the node moments, so results agree with other choices to
+ * rounding, not bit for bit. */
 int dgbgk_set_block_elements(dgbgk_solver *s, int32_t elems_per_group);
 
 /* Autotuner: times `launches` right-hand-side launches on the current state
  * (the state is not modified) for the automatic form and every admissible
- * number of elements per work-group of the fused form (and, in FP64, velocity tiles of Q, Q/2, ...,
- * unless the caller forced the fused form with dgbgk_set_tiling mode 1 or 3),
+ * number of elements per work-group of the fused form (and, in FP64, velocity
+ * tiles of Q, Q/2, ..., unless the caller forced the fused form with
+ * dgbgk_set_tiling mode 1 or 3),
  * keeps the fastest and returns its average launch time in microseconds
  * (optional).  Requires a state (DGBGK_ESTATE otherwise); synchronises the
  * solver's stream. */
