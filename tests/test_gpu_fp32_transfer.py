@@ -7,7 +7,7 @@ import pytest
 
 import workloads
 from paper_2012_13487_amd import binding
-from test_gpu_rows import _spec
+from test_gpu_rows import TOL, _errors, _spec
 
 PRECISIONS = pytest.mark.parametrize("prec", [binding.FP32, binding.FP32_REF], ids=["fp32", "fp32_ref"])
 
@@ -60,3 +60,28 @@ def test_calls_between_steps_leave_the_steps_as_they_are(p, q, nx, ny, prec):
             b.step(4, dt)
         assert np.array_equal(a.get_state(), b.get_state())
         assert a.residual() == b.residual()
+
+
+@pytest.mark.gpu
+@PRECISIONS
+@pytest.mark.parametrize("p,q", [(3, 513), (1, 257)])
+def test_one_element_blocks_share_the_buffer(oracle_mod, p, q, prec):
+    """The block kernels of such velocity counts hand their moments on in the
+    same place: steps with transfers between them against the oracle."""
+    spec = _spec(p, q, 3, 2, "cavity")
+    print(f"[gpu] transfers between steps of blocks {spec.name} precision {prec}", flush=True)
+    g, o = binding.Solver.from_spec(spec, precision=prec), oracle_mod.Oracle.from_spec(spec)
+    g.set_block_elements(1)
+    assert g.step_form()["form"] == 0
+    f = workloads.perturbed_state(9 + q, g.w, g.K, g.Np, amp=0.05)
+    dt = o.stable_dt(0.2)
+    for s in (g, o):
+        s.set_state(f)
+    for call in (g.get_state, lambda: g.rhs(f), g.residual):
+        g.step(3, dt)
+        o.rk4(3, dt)
+        call()
+    r, _ = o.residual()
+    assert abs(g.residual() - r) < TOL[prec] * r
+    er, eu = _errors(g.moments(), o.moments())
+    assert er < TOL[prec] and eu < TOL[prec], (er, eu)
